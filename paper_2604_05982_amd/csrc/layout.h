@@ -75,9 +75,10 @@ enum TaskKind : uint32_t {
 // Extension task sets of the thread-mode kernel, each compiled in only where
 // a launch needs it: the split k-clique bodies alone add private memory and
 // registers to every task of the kernel.
-constexpr uint32_t kExtLists = 1;  // FMM list-building cell pairs, Cilksort sorts and merges
+constexpr uint32_t kExtLists = 1;  // FMM list-building cell pairs
 constexpr uint32_t kExtSplit = 2;  // k-clique with bitset candidate subgraphs (TK_KS_*)
-constexpr uint32_t kExtAll = kExtLists | kExtSplit;
+constexpr uint32_t kExtSort = 4;   // Cilksort sorts and merges
+constexpr uint32_t kExtAll = kExtLists | kExtSplit | kExtSort;
 
 struct alignas(128) DequeMeta {
   int32_t count;   // unclaimed entries (every claim is a CAS on this word)

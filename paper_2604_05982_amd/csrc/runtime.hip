@@ -589,12 +589,18 @@ static int launch_sched(gtap_ctx *c, uint32_t ext = 0) {
           hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatchedNoLocal>), grid, block, 0, c->stream, c->params);
           break;
         default:
-          if (ext == kExtLists)  // FMM list traversal, Cilksort
-            hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtLists>), grid, block, 0, c->stream, c->params);
-          else if (ext != 0)  // and split k-clique
-            hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtAll>), grid, block, 0, c->stream, c->params);
-          else
+          // the smallest compiled extension set that has the batch's kinds
+          if (ext == 0)
             hipLaunchKernelGGL(thread_sched_kernel<4>, grid, block, 0, c->stream, c->params);
+          else if (ext == kExtLists)
+            hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtLists>), grid, block, 0, c->stream, c->params);
+          else if (ext == kExtSort)
+            hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtSort>), grid, block, 0, c->stream, c->params);
+          else if (ext == (kExtLists | kExtSort))
+            hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtLists | kExtSort>), grid, block, 0, c->stream,
+                               c->params);
+          else
+            hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtAll>), grid, block, 0, c->stream, c->params);
           break;
       }
       break;
@@ -1006,7 +1012,8 @@ int gtap_run(gtap_ctx *c) {
   uint32_t ext = 0;  // extension task sets the batch needs
   for (size_t j = 0; j < nj; ++j) {
     any_fmm |= c->pending[j].kind == GTAP_KIND_FMM;
-    if (c->pending[j].kind == GTAP_KIND_FMM || c->pending[j].kind == GTAP_KIND_CILKSORT) ext |= kExtLists;
+    if (c->pending[j].kind == GTAP_KIND_FMM) ext |= kExtLists;
+    if (c->pending[j].kind == GTAP_KIND_CILKSORT) ext |= kExtSort;
     if (c->pending[j].kind == GTAP_KIND_KCLIQUE_SPLIT) ext |= kExtSplit;
   }
   std::vector<void *> ks_mem;

@@ -669,13 +669,15 @@ GTAP_DEV void write_root(const Params &p, uint32_t id, uint32_t j) {
         c.p[1] = static_cast<uint32_t>(job_arg(p, j, 2));
       }
     }
-    if constexpr ((kExt & kExtLists) != 0) {
+    if constexpr ((kExt & kExtSort) != 0) {
       if (jkind == 6) {  // Cilksort: sort the whole array into the key buffer
         kind = TK_SORT;
         c.p[0] = 0;
         c.p[1] = static_cast<uint32_t>(job_arg(p, j, 2));
         c.p[2] = 0;
       }
+    }
+    if constexpr ((kExt & kExtLists) != 0) {
       // FMM in thread mode: the list-building traversal starts at the pair
       // (root, root); a job whose lists the worklist builds has an empty root
       // (a[0] descriptor, a[1] traversal, a[2] = theta_num | theta_den << 8)
@@ -775,7 +777,7 @@ struct LocalCap {
 // kSchedBatchedNoLocal = batched without the private stack) at compile time,
 // so the comparison variants add nothing to the scheduler as designed; kExt
 // adds extension task sets (kExtLists: the FMM list-building cell pairs and
-// their list appends, Cilksort; kExtSplit: split k-clique).
+// their list appends; kExtSort: Cilksort; kExtSplit: split k-clique).
 template <int WPB, uint32_t V = kSchedBatched, uint32_t kExt = 0>
 __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
   constexpr bool kCentral = (V == kSchedCentral);
@@ -1044,13 +1046,26 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
     if constexpr ((kExt & kExtLists) != 0) {
       // FMM list traversal: accepted pairs and leaf pairs go to their lists,
       // through this wavefront's chunks of them
-      const bool em = o.type == OUT_DONE && o.emit != 0;
+      const bool em = o.type == OUT_DONE && (o.emit == 1 || o.emit == 2);
       if (ballot(em) != 0ull) {
         fmm::FmmDesc *D = reinterpret_cast<fmm::FmmDesc *>(pack(o.d[3], o.d[4]));
         const uint64_t pair = (static_cast<uint64_t>(o.d[0]) << 32) | o.d[1];
         fmm::chunks_append(lchunks, D, 0, em && o.emit == 1, pair);
         fmm::chunks_append(lchunks, D, 1, em && o.emit == 2, pair);
       }
+    }
+    if constexpr ((kExt & kExtSort) != 0) {
+      // Cilksort: the lanes' serial sorts and merges, by the whole wavefront
+      const uint64_t m_sort = ballot(o.emit == kEmitSort), m_merge = ballot(o.emit == kEmitMerge);
+      auto span_of = [&](int k) {
+        return cilk::Span{reinterpret_cast<const uint32_t *>(cilk::lane_u64(o.d[0], o.d[1], k)),
+                          reinterpret_cast<const uint32_t *>(cilk::lane_u64(o.d[2], o.d[3], k)),
+                          reinterpret_cast<uint32_t *>(cilk::lane_u64(o.nchild, o.ckind, k)),
+                          static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(o.d[4]), k)),
+                          static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(o.d[5]), k))};
+      };
+      if (m_sort != 0ull) cilk::run_sorts(m_sort, span_of);
+      if (m_merge != 0ull) cilk::run_merges(m_merge, span_of);
     }
     data_words += o.words;
     const uint32_t nfirst = __popcll(ballot(o.first != 0));

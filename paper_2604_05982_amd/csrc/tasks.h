@@ -19,6 +19,7 @@
 #include "fmm_lists.h"
 #include "kclique_bits.h"
 #include "layout.h"
+#include "sort_wave.h"
 #include "wave.h"
 
 namespace gtap {
@@ -60,7 +61,9 @@ struct Outcome {
   uint32_t job;
   uint32_t kind;     // this task's kind
   uint32_t first;    // 1: first execution (resume point 0), 0: continuation
-  uint32_t emit;     // FMM list traversal: 1 = M2L pair, 2 = P2P pair (d[0], d[1]), descriptor d[3..4]
+  uint32_t emit;     // FMM list traversal: 1 = M2L pair, 2 = P2P pair (d[0], d[1]), descriptor d[3..4];
+                     // kEmitSort / kEmitMerge: source addresses d[0..1], d[2..3], key counts d[4], d[5],
+                     // destination address (nchild, ckind)
   uint32_t pc_next;  // OUT_FORK of the extended kinds: resume point after the join (Cilksort sorts fork twice)
   uint32_t words;    // 4-byte words of task data the body read or wrote (k-clique lists), for the byte count
 };
@@ -228,40 +231,31 @@ GTAP_DEV TaskImage load_continuation(const Params &p, uint32_t tid) {
 // a task's destination bit picks one, its sources are in the other.  Keys
 // pass between tasks that may run on different XCDs, so they are read and
 // written with device-coherent accesses (and the scheduler drains a
-// wavefront's writes before its completions reach the join words).
-constexpr uint32_t kSortNet = 64;            // serial sorts: a 64-wide network
+// wavefront's writes before its completions reach the join words).  Serial
+// sorts and merges are only described here (Outcome.emit); the wavefront runs
+// them together (sort_wave.h).
 constexpr uint32_t kMergeD = (1u << 29) - 1;  // merge payload word 4: destination start
+constexpr uint32_t kEmitSort = 3, kEmitMerge = 4;
 
-// Bitonic sorting network on 64 keys held in registers (all indices are
-// compile-time constants after unrolling, so nothing spills to scratch).
-GTAP_DEV void sort_net64(uint32_t *v) {
-#pragma unroll
-  for (uint32_t k = 2; k <= kSortNet; k <<= 1) {
-#pragma unroll
-    for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-#pragma unroll
-      for (uint32_t i = 0; i < kSortNet; ++i) {
-        const uint32_t l = i ^ j;
-        if (l > i) {
-          const uint32_t lo = v[i] < v[l] ? v[i] : v[l], hi = v[i] < v[l] ? v[l] : v[i];
-          const bool up = (i & k) == 0;
-          v[i] = up ? lo : hi;
-          v[l] = up ? hi : lo;
-        }
-      }
-    }
-  }
-}
-
-// Number of keys of the sorted range s[0, n) below v.
+// Number of keys of the sorted range s[0, n) below v.  Seven keys are read at
+// once and the range shrinks to an eighth: the search is a chain of loads
+// from other XCDs' writes (about a microsecond each), a third as long as a
+// bisection's.
 GTAP_DEV uint32_t count_below(const uint32_t *s, uint32_t n, uint32_t v) {
   uint32_t lo = 0, hi = n;
-  while (lo < hi) {
-    const uint32_t mid = lo + (hi - lo) / 2;
-    if (co_ld32(s + mid) < v) lo = mid + 1;
-    else hi = mid;
+  while (hi - lo >= 8) {
+    const uint32_t q = (hi - lo) / 8;
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t i = 1; i < 8; ++i) c += co_ld32(s + lo + i * q) < v ? 1u : 0u;
+    const uint32_t base = lo;
+    if (c > 0) lo = base + c * q + 1;
+    if (c < 7) hi = base + (c + 1) * q;
   }
-  return lo;
+  uint32_t c = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < 7; ++i) c += lo + i < hi && co_ld32(s + lo + i) < v ? 1u : 0u;
+  return lo + c;
 }
 
 // ---------------------------------------------------------------------------
@@ -626,7 +620,7 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
   if constexpr (kExt) {
     o.emit = 0;
     o.pc_next = 1;
-    if constexpr ((kExt & kExtLists) != 0) {
+    if constexpr ((kExt & kExtSort) != 0) {
       if (pc != 0 && kind == TK_SORT) {
         // after the two sorts: merge them back (resume point 2 follows); after
         // the merge: done, the result is the range's length
@@ -673,22 +667,19 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
   const uint32_t p1 = static_cast<uint32_t>(w45), p2 = static_cast<uint32_t>(w45 >> 32);
   const uint32_t p3 = static_cast<uint32_t>(w67), p4 = static_cast<uint32_t>(w67 >> 32);
   if constexpr (kExt) {
-    if constexpr ((kExt & kExtLists) != 0) {
+    if constexpr ((kExt & kExtSort) != 0) {
       if (kind == TK_SORT) {
         // sort(lo, n, dst): serial below the cutoff, else both halves into the
         // other buffer first (resume point 1 merges them)
         const uint32_t lo = p0, n = p1, dst = p2;
         const uint32_t sc = static_cast<uint32_t>(job_arg(p, o.job, 3));
         if (n <= sc) {
-          const uint32_t *X = reinterpret_cast<const uint32_t *>(job_arg(p, o.job, 0));
-          uint32_t *D = reinterpret_cast<uint32_t *>(job_arg(p, o.job, dst ? 1 : 0));
-          uint32_t v[kSortNet];
-  #pragma unroll
-          for (uint32_t i = 0; i < kSortNet; ++i) v[i] = i < n ? co_ld32(X + lo + i) : 0xFFFFFFFFu;
-          sort_net64(v);
-  #pragma unroll
-          for (uint32_t i = 0; i < kSortNet; ++i)
-            if (i < n) co_st32(D + lo + i, v[i]);
+          const uint64_t x = job_arg(p, o.job, 0) + 4ull * lo;
+          const uint64_t d = job_arg(p, o.job, dst ? 1 : 0) + 4ull * lo;
+          o.emit = kEmitSort;
+          o.d[0] = static_cast<uint32_t>(x); o.d[1] = static_cast<uint32_t>(x >> 32);
+          o.d[4] = n;
+          o.nchild = static_cast<uint32_t>(d); o.ckind = static_cast<uint32_t>(d >> 32);
           o.value = n;
           return;
         }
@@ -721,19 +712,13 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
         }
         const uint32_t mc = static_cast<uint32_t>(job_arg(p, o.job, 3) >> 32);
         if (na + nb <= mc) {
-          uint32_t i = 0, j = 0, k = d0;
-          while (i < na && j < nb) {
-            const uint32_t x = co_ld32(S + a0 + i), y = co_ld32(S + b0 + j);
-            if (y < x) {
-              co_st32(D + k++, y);
-              ++j;
-            } else {
-              co_st32(D + k++, x);
-              ++i;
-            }
-          }
-          while (i < na) co_st32(D + k++, co_ld32(S + a0 + i++));
-          while (j < nb) co_st32(D + k++, co_ld32(S + b0 + j++));
+          const uint64_t a = reinterpret_cast<uint64_t>(S + a0), b = reinterpret_cast<uint64_t>(S + b0);
+          const uint64_t d = reinterpret_cast<uint64_t>(D + d0);
+          o.emit = kEmitMerge;
+          o.d[0] = static_cast<uint32_t>(a); o.d[1] = static_cast<uint32_t>(a >> 32);
+          o.d[2] = static_cast<uint32_t>(b); o.d[3] = static_cast<uint32_t>(b >> 32);
+          o.d[4] = na; o.d[5] = nb;
+          o.nchild = static_cast<uint32_t>(d); o.ckind = static_cast<uint32_t>(d >> 32);
           return;
         }
         o.type = OUT_FORK;
@@ -977,7 +962,7 @@ template <uint32_t kExt = 0>
 GTAP_DEV uint32_t child_class(const Params &p, uint32_t job, uint32_t ckind, const ChildInit &c) {
   if (p.Q <= 1) return 0;
   if constexpr (kExt) {
-    if constexpr ((kExt & kExtLists) != 0) {
+    if constexpr ((kExt & kExtSort) != 0) {
       if (p.daq_policy == 3) {  // Cilksort: recursive 0, serial sort 1, serial merge 2
         const uint64_t cut = job_arg(p, job, 3);
         if (ckind == TK_SORT) return (c.p[1] <= static_cast<uint32_t>(cut) ? 1u : 0u) % p.Q;
@@ -1045,7 +1030,7 @@ template <uint32_t kExt = 0>
 GTAP_DEV void make_child(uint32_t ckind, const Words<6> &d, uint32_t j, ChildInit &c) {
   for (uint32_t i = 0; i < kPayloadWords; ++i) c.p[i] = 0;
   if constexpr (kExt) {
-    if constexpr ((kExt & kExtLists) != 0) {
+    if constexpr ((kExt & kExtSort) != 0) {
       if (ckind == TK_SORT) {  // half j into the other buffer
         const uint32_t h = d[1] / 2;
         c.p[0] = d[0] + (j ? h : 0u);
