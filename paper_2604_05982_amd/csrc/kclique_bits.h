@@ -14,9 +14,9 @@
 // A node of the search splits when its candidate set is larger than the
 // threshold t (the spawn-time cost estimate): it stores its state in its frame
 // and forks one task per branch, and every child applies the same test.  A
-// node at or below the threshold is finished by one lane in place: its
-// candidates are renumbered into a private 64 x 64 matrix (one word per row)
-// and the recursion runs on registers and a private stack.
+// node at or below the threshold is finished in place: its candidates are
+// renumbered into a 64 x 64 matrix (one word per row) in LDS and the lanes of
+// the wavefront share the search (kclique_wave.h).
 //
 //   orientation   node (S, l) counts l-cliques of the DAG on S:
 //                 K(S,1) = |S|, K(S,l) = sum over x in S of K(S /\ row x, l-1)
@@ -58,20 +58,6 @@ __host__ __device__ inline uint32_t buffer_ints(uint32_t D) {
 }
 
 GTAP_DEV uint64_t low_mask(uint32_t m) { return m >= 64 ? ~0ull : ((1ull << m) - 1); }
-
-// Position of the j-th set bit (from 0) of a W-word set.
-GTAP_DEV uint32_t select_bit(const uint64_t *s, uint32_t W, uint32_t j) {
-  for (uint32_t w = 0; w < W; ++w) {
-    uint64_t t = s[w];
-    const uint32_t n = __popcll(t);
-    if (j < n) {
-      for (uint32_t i = 0; i < j; ++i) t &= t - 1;
-      return w * 64 + __builtin_ctzll(t);
-    }
-    j -= n;
-  }
-  return 0;
-}
 
 // binom(n, r), exact whenever the result fits in 64 bits: C(n-r+i, i) from
 // C(n-r+i-1, i-1) times (n-r+i) over i; a large partial value is divided by
@@ -231,34 +217,6 @@ GTAP_DEV int64_t sct_count(const uint64_t *A, uint64_t P0, uint32_t h0, uint32_t
       break;
     }
   }
-}
-
-// Renumber the members of the W-word set s (at most 64 of them) into one-word
-// rows A, from the c x W matrix `rows` (device-coherent reads).  Returns the
-// member count.
-GTAP_DEV uint32_t compact(const uint64_t *rows, uint32_t W, const uint64_t *s, uint64_t *A) {
-  uint32_t pre[kMaxW];
-  uint32_t m = 0;
-  for (uint32_t w = 0; w < W; ++w) {
-    pre[w] = m;
-    m += __popcll(s[w]);
-  }
-  uint32_t a = 0;
-  for (uint32_t w = 0; w < W; ++w) {
-    for (uint64_t t = s[w]; t; t &= t - 1) {
-      const uint32_t x = w * 64 + __builtin_ctzll(t);
-      uint64_t r = 0;
-      for (uint32_t v = 0; v < W; ++v) {
-        uint64_t u = co_ld64(rows + static_cast<size_t>(x) * W + v) & s[v];
-        for (; u; u &= u - 1) {
-          const uint32_t b = __builtin_ctzll(u);
-          r |= 1ull << (pre[v] + __popcll(s[v] & low_mask(b)));
-        }
-      }
-      A[a++] = r;
-    }
-  }
-  return m;
 }
 
 }  // namespace kcs

@@ -596,6 +596,8 @@ static int launch_sched(gtap_ctx *c, uint32_t ext = 0) {
             hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtLists>), grid, block, 0, c->stream, c->params);
           else if (ext == kExtSort)
             hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtSort>), grid, block, 0, c->stream, c->params);
+          else if (ext == kExtSplit)
+            hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtSplit>), grid, block, 0, c->stream, c->params);
           else if (ext == (kExtLists | kExtSort))
             hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtLists | kExtSort>), grid, block, 0, c->stream,
                                c->params);

@@ -22,6 +22,7 @@
 // a device error word and every wavefront leaves the loop (Sec. 4: overflow
 // aborts with a structured report).
 #pragma once
+#include "kclique_wave.h"
 #include "layout.h"
 #include "tasks.h"
 #include "wave.h"
@@ -606,26 +607,6 @@ GTAP_DEV int32_t central_pop(const Params &p, uint32_t me, uint32_t cnt, uint32_
 }
 
 // ---------------------------------------------------------------------------
-// Owner (forking lane) of child g0 + lane, for one 64-child chunk of a
-// wavefront's forks: each forking lane whose first child falls in the chunk
-// marks that slot, and a prefix maximum over the lanes carries every mark to
-// the children after it; `carry` holds the owner of the chunk's first child
-// when no mark precedes it (the previous chunk's last owner) and is updated.
-// One LDS round trip instead of a binary search over the offsets.  Must be
-// called with every lane active.
-GTAP_DEV uint32_t chunk_owner(uint32_t *mark, uint32_t nchild, uint32_t off, uint32_t g0, uint32_t &carry) {
-  const uint32_t ln = lane_id();
-  mark[ln] = 0;
-  wave_sync();
-  if (nchild > 0 && off >= g0 && off - g0 < kWave) mark[off - g0] = ln + 1;
-  wave_sync();
-  const uint32_t m = wave_inclusive_max(mark[ln]);
-  const uint32_t own = m ? m - 1 : carry;
-  carry = __builtin_amdgcn_readlane(own, 63);
-  wave_sync();
-  return own;
-}
-
 // Root frame of job slot j (payload from the job's arguments).
 template <uint32_t kExt = 0>
 GTAP_DEV void write_root(const Params &p, uint32_t id, uint32_t j) {
@@ -767,10 +748,11 @@ GTAP_DEV uint32_t admit_jobs(const Params &p, WaveLds &L, uint32_t me, PoolView 
 // Capacity of a wavefront's private LDS task stack (task images, 32 bytes
 // each): 16 KB per wavefront, 8 KB with eight wavefronts per workgroup (the
 // largest power of two with which one such workgroup, 147 KB of LDS, still
-// fits a compute unit's 160 KB).
-template <int WPB>
+// fits a compute unit's 160 KB) and where the split k-clique bodies need the
+// room for a vertex's matrix.
+template <int WPB, uint32_t kExt>
 struct LocalCap {
-  static constexpr uint32_t v = WPB >= 8 ? 256u : 512u;
+  static constexpr uint32_t v = WPB >= 8 || (kExt & kExtSplit) != 0 ? 256u : 512u;
 };
 
 // V selects the queue management (kSchedBatched, kSchedSingle, kSchedCentral;
@@ -784,12 +766,13 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
   constexpr bool kSingle = (V == kSchedSingle);
   constexpr bool kNoLocal = (V != kSchedBatched);
   __shared__ WaveLds lds_all[WPB];
+  __shared__ kcw::Lds ks_all[(kExt & kExtSplit) != 0 ? WPB : 1];  // (no LDS where nothing refers to it)
   // Private task stack: children a wavefront cannot run in its lanes this
   // iteration stay here as frameless images and are popped (newest first)
   // before the shared deque; only the oldest are exposed to thieves, with
   // frames, when the stack overflows or when the wavefront's deque runs dry
   // while another wavefront is looking for work.
-  constexpr uint32_t LC = LocalCap<WPB>::v;
+  constexpr uint32_t LC = LocalCap<WPB, kExt>::v;
   __shared__ uint4 lstk_all[WPB][2 * LC];
   const uint32_t wv = threadIdx.x >> 6;
   WaveLds &L = lds_all[wv];
@@ -1066,6 +1049,16 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
       };
       if (m_sort != 0ull) cilk::run_sorts(m_sort, span_of);
       if (m_merge != 0ull) cilk::run_merges(m_merge, span_of);
+    }
+    if constexpr ((kExt & kExtSplit) != 0) {
+      // split k-clique: rows, vertices in place and searches, by the whole wavefront
+      kcw::Lds &K = ks_all[wv];
+      const uint64_t m_clear = ballot(o.emit == kEmitClear), m_row = ballot(o.emit == kEmitRow);
+      const uint64_t m_vertex = ballot(o.emit == kEmitVertex), m_search = ballot(o.emit == kEmitSearch);
+      if (m_clear != 0ull) kcw::clear_mats(p.jobs, m_clear, o.job, o.d[0]);
+      if (m_row != 0ull) kcw::run_rows(K, p.jobs, m_row, o.job, o.d[0], o.d[1], o.words);
+      if (m_vertex != 0ull) kcw::run_vertices(K, p.jobs, m_vertex, o.job, o.d[1], o.d[2], o.value, o.words);
+      if (m_search != 0ull) kcw::run_search(p, K, m_search, tid, o);
     }
     data_words += o.words;
     const uint32_t nfirst = __popcll(ballot(o.first != 0));

@@ -63,7 +63,7 @@ struct Outcome {
   uint32_t first;    // 1: first execution (resume point 0), 0: continuation
   uint32_t emit;     // FMM list traversal: 1 = M2L pair, 2 = P2P pair (d[0], d[1]), descriptor d[3..4];
                      // kEmitSort / kEmitMerge: source addresses d[0..1], d[2..3], key counts d[4], d[5],
-                     // destination address (nchild, ckind)
+                     // destination address (nchild, ckind); kEmitRow .. kEmitClear: split k-clique
   uint32_t pc_next;  // OUT_FORK of the extended kinds: resume point after the join (Cilksort sorts fork twice)
   uint32_t words;    // 4-byte words of task data the body read or wrote (k-clique lists), for the byte count
 };
@@ -262,338 +262,24 @@ GTAP_DEV uint32_t count_below(const uint32_t *s, uint32_t n, uint32_t v) {
 // k-clique counting with bitset candidate subgraphs and cost-threshold
 // splitting (Sec. 6.4.2); the encoding is described in kclique_bits.h.  Job
 // arguments: 0 row_ptr, 1 col, 2 n, 3 k, 4 range_leaf, 5 max out-degree,
-// 6 threshold | algorithm << 8 (0 orientation, 1 pivoting).
-struct KsJob {
-  const int32_t *rp;
-  const int32_t *col;
-  uint64_t *mat;   // job argument 7: n+1 vertex offsets, then the bit matrices
-  uint32_t n;
-  uint32_t kk;     // k - 2: clique size inside an edge's candidate set
-  uint32_t thr;
-  bool pivot;
-};
-GTAP_DEV KsJob ks_job(const Params &p, uint32_t job) {
-  const uint64_t a6 = job_arg(p, job, 6);
-  return KsJob{reinterpret_cast<const int32_t *>(job_arg(p, job, 0)),
-               reinterpret_cast<const int32_t *>(job_arg(p, job, 1)),
-               reinterpret_cast<uint64_t *>(job_arg(p, job, 7)), static_cast<uint32_t>(job_arg(p, job, 2)),
-               static_cast<uint32_t>(job_arg(p, job, 3)) - 2, static_cast<uint32_t>(a6 & 0xFFu),
-               ((a6 >> 8) & 1u) != 0};
-}
+// 6 threshold | algorithm << 8 (0 orientation, 1 pivoting), 7 the vertex
+// offsets and bit matrices.  The bodies that touch lists or matrices are only
+// described here (Outcome.emit, d[0..1] = vertex, index); the wavefront runs
+// them together (kclique_wave.h).
+constexpr uint32_t kEmitRow = 5;     // one row of a vertex's matrix
+constexpr uint32_t kEmitVertex = 6;  // a vertex counted in place: d[1] = first out-list position, d[2] = out-degree
+constexpr uint32_t kEmitSearch = 7;  // an edge, a heavy edge's root or a branch
+constexpr uint32_t kEmitClear = 8;   // pivoting: a vertex about to fork row tasks, whose U is cleared first
 
-// Vertex u's bit matrices: D (row i: the members of N+(u) that are
-// out-neighbours of its i-th member), then for pivoting U (D or its
-// transpose); d x W words each.  The offsets are read coherently like all
-// job data.
-struct KsMat {
-  uint64_t *D;
-  uint64_t *rows;  // the rows the search uses: U for pivoting, else D
-  uint32_t d, W;
-};
-GTAP_DEV KsMat ks_mat(const KsJob &J, uint32_t u) {
-  const uint32_t d = static_cast<uint32_t>(J.rp[u + 1] - J.rp[u]);
-  const uint32_t W = (d + 63) / 64;
-  uint64_t *D = J.mat + (J.n + 1) + co_ld64(J.mat + u);
-  return KsMat{D, J.pivot ? D + static_cast<size_t>(d) * W : D, d, W};
-}
-
-// Store a node's state at buf (device-coherent: its children read it).
-GTAP_DEV void ks_store_node(uint32_t *buf, uint64_t meta, const uint64_t *P, const uint64_t *R, uint32_t W,
-                            bool with_r) {
-  uint64_t *b = reinterpret_cast<uint64_t *>(buf);
-  co_st64(b, meta);
-  for (uint32_t w = 0; w < W; ++w) co_st64(b + 1 + w, P[w]);
-  if (with_r)
-    for (uint32_t w = 0; w < W; ++w) co_st64(b + 1 + W + w, R[w]);
-}
-
-// Pivot of a split pivoting node: the member of P with the most neighbours in
-// P, the lowest on ties; R receives its non-neighbours other than itself.
-GTAP_DEV uint32_t ks_pivot(const uint64_t *rows, uint32_t W, const uint64_t *P, uint64_t *R) {
-  uint32_t best = 0;
-  int32_t bd = -1;
-  for (uint32_t w = 0; w < W; ++w) {
-    for (uint64_t t = P[w]; t; t &= t - 1) {
-      const uint32_t x = w * 64 + __builtin_ctzll(t);
-      int32_t d = 0;
-      for (uint32_t v = 0; v < W; ++v) d += __popcll(P[v] & co_ld64(rows + static_cast<size_t>(x) * W + v));
-      if (d > bd) {
-        bd = d;
-        best = x;
-      }
-    }
-  }
-  for (uint32_t v = 0; v < W; ++v) R[v] = P[v] & ~co_ld64(rows + static_cast<size_t>(best) * W + v);
-  R[best >> 6] &= ~(1ull << (best & 63));
-  return best;
-}
-
-// Row task (u, i): row i of u's matrix, from N+(u) /\ N+(x), x = N+(u)[i],
-// galloping from the shorter list; for pivoting also ORed into U both ways
-// (U was cleared by the vertex task).
-GTAP_DEV void ks_row(const Params &p, Outcome &o, uint32_t u, uint32_t i) {
-  const KsJob J = ks_job(p, o.job);
-  const KsMat M = ks_mat(J, u);
-  const uint32_t d = M.d, W = M.W;
-  const int32_t *nu = J.col + J.rp[u];
-  const int32_t x = nu[i];
-  const int32_t *nx = J.col + J.rp[x];
-  const uint32_t dx = static_cast<uint32_t>(J.rp[x + 1] - J.rp[x]);
-  uint64_t *D = M.D + static_cast<size_t>(i) * W;
-  uint64_t *U = M.rows;
-  o.words = 4 + d + dx + (J.pivot ? 4 : 2) * W;  // row bounds, both lists, the row (and U's) written
-  uint32_t cw = 0;
-  uint64_t acc = 0;
-  auto flush = [&]() {  // word cw of row i is complete
-    co_st64(D + cw, acc);
-    if (J.pivot && acc) fetch_or_relaxed(U + static_cast<size_t>(i) * W + cw, acc);
-    ++cw;
-    acc = 0;
-  };
-  auto hit = [&](uint32_t j) {  // j ascending
-    while ((j >> 6) > cw) flush();
-    acc |= 1ull << (j & 63);
-    if (J.pivot) fetch_or_relaxed(U + static_cast<size_t>(j) * W + (i >> 6), static_cast<uint64_t>(1) << (i & 63));
-  };
-  if (d <= dx) {  // each member of N+(u), galloped to in N+(x)
-    uint32_t t = 0;
-    for (uint32_t j = 0; j < d && t < dx; ++j) {
-      t = kcs::gallop(nx, t, dx, nu[j]);
-      if (t < dx && nx[t] == nu[j]) {
-        hit(j);
-        ++t;
-      }
-    }
-  } else {  // each out-neighbour of x, galloped to in N+(u)
-    uint32_t j = 0;
-    for (uint32_t t = 0; t < dx && j < d; ++t) {
-      j = kcs::gallop(nu, j, d, nx[t]);
-      if (j < d && nu[j] == nx[t]) {
-        hit(j);
-        ++j;
-      }
-    }
-  }
-  while (cw < W) flush();
-}
-
-// A vertex with d <= threshold out-neighbours (k >= 4): its matrix in private
-// one-word rows (galloping as the row tasks do), then every edge's search in
-// place: edge i's candidates are row i.
-GTAP_DEV int64_t ks_vertex_in_place(const KsJob &J, uint32_t u, uint32_t d, uint32_t &words) {
-  const int32_t *nu = J.col + J.rp[u];
-  uint64_t A[kcs::kMaxThr], B[kcs::kMaxThr];
-  words += d;
-  for (uint32_t i = 0; i < d; ++i) {
-    const int32_t x = nu[i];
-    const int32_t *nx = J.col + J.rp[x];
-    const uint32_t dx = static_cast<uint32_t>(J.rp[x + 1] - J.rp[x]);
-    words += 2 + dx;
-    uint64_t r = 0;
-    if (d <= dx) {
-      uint32_t t = 0;
-      for (uint32_t j = 0; j < d && t < dx; ++j) {
-        t = kcs::gallop(nx, t, dx, nu[j]);
-        if (t < dx && nx[t] == nu[j]) {
-          r |= 1ull << j;
-          ++t;
-        }
-      }
-    } else {
-      uint32_t j = 0;
-      for (uint32_t t = 0; t < dx && j < d; ++t) {
-        j = kcs::gallop(nu, j, d, nx[t]);
-        if (j < d && nu[j] == nx[t]) {
-          r |= 1ull << j;
-          ++j;
-        }
-      }
-    }
-    A[i] = r;
-    B[i] = r;
-  }
-  if (J.pivot)  // both directions
-    for (uint32_t i = 0; i < d; ++i)
-      for (uint64_t t = A[i]; t; t &= t - 1) B[__builtin_ctzll(t)] |= 1ull << i;
-  int64_t total = 0;
-  for (uint32_t i = 0; i < d; ++i) {
-    if (static_cast<uint32_t>(__popcll(A[i])) < J.kk) continue;
-    total += J.pivot ? kcs::sct_count(B, A[i], 0, 0, J.kk) : kcs::dag_count(A, A[i], J.kk);
-  }
-  return total;
-}
-
-// Edge task (u, i): the i-th out-neighbour v of u.  k = 3: |N+(u) /\ N+(v)|.
-// Otherwise its candidates are row i of u's matrix: few -> renumbered into a
-// private one-word matrix and counted in place; more than the threshold ->
-// one child task takes the search over.
-GTAP_DEV void ks_edge(const Params &p, Outcome &o, uint32_t u, uint32_t i) {
-  const KsJob J = ks_job(p, o.job);
-  if (J.kk == 1) {
-    const int32_t s0 = J.rp[u];
-    const int32_t v = J.col[s0 + i];
-    const uint32_t du = static_cast<uint32_t>(J.rp[u + 1] - s0), dv = static_cast<uint32_t>(J.rp[v + 1] - J.rp[v]);
-    o.words = 5 + du + dv;
-    o.value = kcs::isect(J.col + s0, du, J.col + J.rp[v], dv, nullptr, 0);
-    return;
-  }
-  const KsMat M = ks_mat(J, u);
-  const uint32_t W = M.W;
-  o.words = 4 + 2 * W;  // row bounds, matrix offset, the edge's row
-  uint64_t S[kcs::kMaxW];
-  uint32_t c = 0;
-  for (uint32_t w = 0; w < W; ++w) {
-    S[w] = co_ld64(M.D + static_cast<size_t>(i) * W + w);
-    c += __popcll(S[w]);
-  }
-  if (c < J.kk) return;
-  if (!J.pivot && J.kk == 2) {  // directed edges inside C
-    o.words += 2 * W * c;  // the candidates' rows
-    int64_t e = 0;
-    for (uint32_t w = 0; w < W; ++w)
-      for (uint64_t t = S[w]; t; t &= t - 1) {
-        const uint32_t y = w * 64 + __builtin_ctzll(t);
-        for (uint32_t v = 0; v < W; ++v) e += __popcll(S[v] & co_ld64(M.D + static_cast<size_t>(y) * W + v));
-      }
-    o.value = e;
-    return;
-  }
-  if (c > J.thr) {
-    o.type = OUT_FORK;
-    o.nchild = 1;
-    o.ckind = TK_KS_HEAVY;
-    o.big = 1;
-    o.d[0] = u;
-    o.d[1] = i;
-    return;
-  }
-  uint64_t A[kcs::kMaxThr];
-  o.words += 2 * W * c;  // the candidates' rows
-  kcs::compact(M.rows, W, S, A);
-  const uint64_t all = kcs::low_mask(c);
-  o.value = J.pivot ? kcs::sct_count(A, all, 0, 0, J.kk) : kcs::dag_count(A, all, J.kk);
-}
-
-// Root node of a heavy edge's search (its big frame holds the node state;
-// the matrix is u's): one task per branch.
-GTAP_DEV void ks_heavy(const Params &p, uint32_t *f, Outcome &o, uint32_t u, uint32_t i) {
-  const KsJob J = ks_job(p, o.job);
-  const KsMat M = ks_mat(J, u);
-  const uint32_t W = M.W;
-  uint64_t P[kcs::kMaxW], R[kcs::kMaxW];
-  uint32_t c = 0;
-  for (uint32_t w = 0; w < W; ++w) {
-    P[w] = co_ld64(M.D + static_cast<size_t>(i) * W + w);
-    c += __popcll(P[w]);
-  }
-  uint64_t meta = J.kk;
-  uint32_t nchild = c;
-  o.words = 4 + 2 * W + (J.pivot ? 2 * W * (c + 1) + 2 + 4 * W : 2 + 2 * W);  // row; pivot rows; node state
-  if (J.pivot) {
-    const uint32_t piv = ks_pivot(M.rows, W, P, R);
-    meta = static_cast<uint64_t>(piv) << 32;  // no held vertices, no pivots yet
-    nchild = 1;
-    for (uint32_t w = 0; w < W; ++w) nchild += __popcll(R[w]);
-  }
-  ks_store_node(f + FW_BUF, meta, P, R, W, J.pivot);
-  o.type = OUT_FORK;
-  o.nchild = nchild;
-  o.ckind = TK_KS_NODE;
-  o.big = (J.pivot || J.kk - 1 >= 3) ? 1u : 0u;  // children that may split keep state in a big frame
-  o.d[0] = u;
-  o.d[1] = 0;
-}
-
-// Branch j of a node that split: u is the vertex whose matrix the search
-// uses, ns the node state's offset in the parent's buffer.
-GTAP_DEV void ks_node(const Params &p, uint32_t *f, Outcome &o, uint32_t u, uint32_t j, uint32_t ns) {
-  const KsJob J = ks_job(p, o.job);
-  const KsMat M = ks_mat(J, u);
-  const uint32_t W = M.W;
-  const uint64_t *rows = M.rows;
-  const uint64_t *pb = reinterpret_cast<const uint64_t *>(frame_ptr(p, o.parent) + FW_BUF + ns);
-  const uint64_t meta = co_ld64(pb);
-  uint64_t P[kcs::kMaxW], S[kcs::kMaxW], R[kcs::kMaxW];
-  for (uint32_t w = 0; w < W; ++w) P[w] = co_ld64(pb + 1 + w);
-  o.words = 6 + 4 * W;  // row bounds, matrix offset, node meta and set, one row
-  uint32_t m = 0;
-  uint64_t A[kcs::kMaxThr];
-  if (!J.pivot) {
-    const uint32_t l = static_cast<uint32_t>(meta & 0xFFFFu) - 1;
-    const uint32_t x = kcs::select_bit(P, W, j);
-    for (uint32_t w = 0; w < W; ++w) {
-      S[w] = P[w] & co_ld64(rows + static_cast<size_t>(x) * W + w);
-      m += __popcll(S[w]);
-    }
-    if (l == 1) {
-      o.value = m;
-      return;
-    }
-    if (m < l) return;
-    o.words += 2 * W * m;  // the rows of the node's candidates
-    if (l == 2) {  // directed edges inside S
-      int64_t e = 0;
-      for (uint32_t w = 0; w < W; ++w)
-        for (uint64_t t = S[w]; t; t &= t - 1) {
-          const uint32_t y = w * 64 + __builtin_ctzll(t);
-          for (uint32_t v = 0; v < W; ++v) e += __popcll(S[v] & co_ld64(rows + static_cast<size_t>(y) * W + v));
-        }
-      o.value = e;
-      return;
-    }
-    if (m <= J.thr) {
-      kcs::compact(rows, W, S, A);
-      o.value = kcs::dag_count(A, kcs::low_mask(m), l);
-      return;
-    }
-    ks_store_node(f + FW_BUF, l, S, S, W, false);
-    o.type = OUT_FORK;
-    o.nchild = m;
-    o.big = l - 1 >= 3 ? 1u : 0u;  // level <= 2 is always counted in place
-  } else {
-    uint32_t h = static_cast<uint32_t>(meta & 0xFFFFu), q = static_cast<uint32_t>((meta >> 16) & 0xFFFFu);
-    const uint32_t piv = static_cast<uint32_t>(meta >> 32);
-    if (j == 0) {  // the pivot branch
-      for (uint32_t w = 0; w < W; ++w) S[w] = P[w] & co_ld64(rows + static_cast<size_t>(piv) * W + w);
-      q += 1;
-    } else {  // the (j-1)-th non-neighbour of the pivot, held
-      for (uint32_t w = 0; w < W; ++w) R[w] = co_ld64(pb + 1 + W + w);
-      const uint32_t x = kcs::select_bit(R, W, j - 1);
-      for (uint32_t w = 0; w < W; ++w) {
-        const uint64_t before = w < (x >> 6) ? R[w] : w == (x >> 6) ? (R[w] & kcs::low_mask(x & 63)) : 0ull;
-        S[w] = P[w] & ~before & co_ld64(rows + static_cast<size_t>(x) * W + w);
-      }
-      S[piv >> 6] &= ~(1ull << (piv & 63));
-      h += 1;
-    }
-    for (uint32_t w = 0; w < W; ++w) m += __popcll(S[w]);
-    if (h == J.kk) {
-      o.value = 1;
-      return;
-    }
-    if (m == 0) {
-      o.value = kcs::binom(q, J.kk - h);
-      return;
-    }
-    if (m + q < J.kk - h) return;
-    o.words += 2 * W * (m + (j == 0 ? 0 : 1));  // the candidates' rows (and R)
-    if (m <= J.thr) {
-      kcs::compact(rows, W, S, A);
-      o.value = kcs::sct_count(A, kcs::low_mask(m), h, q, J.kk);
-      return;
-    }
-    const uint32_t np = ks_pivot(rows, W, S, R);
-    ks_store_node(f + FW_BUF, h | (static_cast<uint64_t>(q) << 16) | (static_cast<uint64_t>(np) << 32), S, R, W,
-                  true);
-    uint32_t nchild = 1;
-    for (uint32_t w = 0; w < W; ++w) nchild += __popcll(R[w]);
-    o.type = OUT_FORK;
-    o.nchild = nchild;
-    o.big = 1;
-  }
-  o.ckind = TK_KS_NODE;
-  o.d[0] = u;
-  o.d[1] = 0;
+// Edge (u, i), k = 3: |N+(u) /\ N+(v)|, v = the i-th out-neighbour of u.
+GTAP_DEV void ks_edge3(const Params &p, Outcome &o, uint32_t u, uint32_t i) {
+  const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 0));
+  const int32_t *col = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 1));
+  const int32_t s0 = rp[u];
+  const int32_t v = col[s0 + i];
+  const uint32_t du = static_cast<uint32_t>(rp[u + 1] - s0), dv = static_cast<uint32_t>(rp[v + 1] - rp[v]);
+  o.words = 5 + du + dv;
+  o.value = kcs::isect(col + s0, du, col + rp[v], dv, nullptr, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -760,34 +446,29 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
           o.pc_next = 2;
           return;
         }
-        const KsJob J = ks_job(p, o.job);
-        if (deg <= J.thr) {  // few out-neighbours: the whole vertex in place, one-word rows
+        const uint64_t a6 = job_arg(p, o.job, 6);
+        if (deg <= static_cast<uint32_t>(a6 & 0xFFu)) {  // few out-neighbours: the whole vertex in place
           o.type = OUT_DONE;
-          o.value = ks_vertex_in_place(J, p0, deg, o.words);
+          o.emit = kEmitVertex;
+          o.d[1] = static_cast<uint32_t>(rp[p0]);
+          o.d[2] = deg;
           return;
         }
-        if (J.pivot) {  // U is built by atomic ORs: cleared first
-          const KsMat M = ks_mat(J, p0);
-          for (uint32_t x = 0; x < deg * M.W; ++x) co_st64(M.rows + x, 0ull);
-          o.words += 2 * deg * M.W;
+        if ((a6 >> 8) & 1u) {
+          o.emit = kEmitClear;
+          o.words += 2 * deg * ((deg + 63) / 64);
         }
         o.ckind = TK_KS_ROW;
         return;
       }
-      if (kind == TK_KS_ROW) {
-        ks_row(p, o, p0, p1);
-        return;
-      }
-      if (kind == TK_KS_EDGE) {
-        ks_edge(p, o, p0, p1);
-        return;
-      }
-      if (kind == TK_KS_HEAVY) {
-        ks_heavy(p, f, o, p0, p1);
-        return;
-      }
-      if (kind == TK_KS_NODE) {
-        ks_node(p, f, o, p0, p1, p2);
+      if (kind == TK_KS_ROW || kind == TK_KS_EDGE || kind == TK_KS_HEAVY || kind == TK_KS_NODE) {
+        if (kind == TK_KS_EDGE && job_arg(p, o.job, 3) == 3) {
+          ks_edge3(p, o, p0, p1);
+          return;
+        }
+        o.emit = kind == TK_KS_ROW ? kEmitRow : kEmitSearch;
+        o.d[0] = p0;
+        o.d[1] = p1;
         return;
       }
     }
@@ -982,17 +663,20 @@ GTAP_DEV uint32_t child_class(const Params &p, uint32_t job, uint32_t ckind, con
         // ranges, row tasks, a heavy edge's search and its branches in the
         // highest class
         if (ckind != TK_KS_EDGE && ckind != TK_KS_VERTEX) return p.Q - 1;
-        const KsJob J = ks_job(p, job);
+        const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, job, 0));
         const uint32_t u = c.p[0];
-        if (ckind == TK_KS_VERTEX) return bucket_of(p, static_cast<uint32_t>(J.rp[u + 1] - J.rp[u]));
-        if (J.kk >= 2) {
-          const KsMat M = ks_mat(J, u);
+        const uint32_t du = static_cast<uint32_t>(rp[u + 1] - rp[u]);
+        if (ckind == TK_KS_VERTEX) return bucket_of(p, du);
+        if (job_arg(p, job, 3) >= 4) {
+          const uint64_t *mat = reinterpret_cast<const uint64_t *>(job_arg(p, job, 7));
+          const uint32_t W = (du + 63) / 64;
+          const uint64_t *row = mat + (job_arg(p, job, 2) + 1) + co_ld64(mat + u) + static_cast<size_t>(c.p[1]) * W;
           uint32_t n = 0;
-          for (uint32_t w = 0; w < M.W; ++w) n += __popcll(co_ld64(M.D + static_cast<size_t>(c.p[1]) * M.W + w));
+          for (uint32_t w = 0; w < W; ++w) n += __popcll(co_ld64(row + w));
           return bucket_of(p, n);
         }
-        const int32_t v = J.col[J.rp[u] + c.p[1]];
-        const uint32_t du = static_cast<uint32_t>(J.rp[u + 1] - J.rp[u]), dv = static_cast<uint32_t>(J.rp[v + 1] - J.rp[v]);
+        const int32_t v = reinterpret_cast<const int32_t *>(job_arg(p, job, 1))[rp[u] + c.p[1]];
+        const uint32_t dv = static_cast<uint32_t>(rp[v + 1] - rp[v]);
         return bucket_of(p, du < dv ? du : dv);
       }
     }

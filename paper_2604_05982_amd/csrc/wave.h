@@ -193,6 +193,26 @@ GTAP_DEV void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Owner lane of position g0 + lane of a concatenation of per-lane runs (this
+// lane's: `n` positions from `off`), for one 64-position chunk: each lane whose
+// run starts in the chunk marks that position (LDS, 64 words), and a prefix
+// maximum carries every mark to the positions after it; `carry` holds the
+// owner of the chunk's first position when no mark precedes it (the previous
+// chunk's last owner) and is updated.  One LDS round trip instead of a binary
+// search over the offsets.  Must be called with every lane active.
+GTAP_DEV uint32_t chunk_owner(uint32_t *mark, uint32_t n, uint32_t off, uint32_t g0, uint32_t &carry) {
+  const uint32_t ln = lane_id();
+  mark[ln] = 0;
+  wave_sync();
+  if (n > 0 && off >= g0 && off - g0 < kWave) mark[off - g0] = ln + 1;
+  wave_sync();
+  const uint32_t m = wave_inclusive_max(mark[ln]);
+  const uint32_t own = m ? m - 1 : carry;
+  carry = __builtin_amdgcn_readlane(own, 63);
+  wave_sync();
+  return own;
+}
+
 // Constant-rate device clock (rate: hipDeviceAttributeWallClockRate).
 GTAP_DEV uint64_t wall_ticks() { return __builtin_amdgcn_s_memrealtime(); }
 
