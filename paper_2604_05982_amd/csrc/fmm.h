@@ -274,123 +274,207 @@ __global__ void k_level_write(int32_t *cell, int32_t *parent, int32_t lo, int32_
   }
 }
 
-// ---- upward pass ----------------------------------------------------------------
-GTAP_DEV void powers(double v, double *pw) {
+// ---- translations -----------------------------------------------------------------
+// Binomial re-centring of a cell's 84 coefficients held in registers, one axis
+// after another (every index is a compile-time constant): 126 multiply-adds
+// an axis instead of the full triple sum's 1,716 (M2M) per coefficient set.
+constexpr Tables kHostTab = make_tables();
+
+template <int AXIS>
+GTAP_DEV void shift_moments(double *q, double s) {  // Q'_b = sum_i C(b, i) s^(b - i) Q_i
+  double pw[kP + 1];
   pw[0] = 1.0;
 #pragma unroll
-  for (int i = 1; i <= kP; ++i) pw[i] = pw[i - 1] * v;
+  for (int i = 1; i <= kP; ++i) pw[i] = pw[i - 1] * s;
+#pragma unroll
+  for (int e = kP; e >= 1; --e) {  // descending: the lower exponents are still the old ones
+#pragma unroll
+    for (int t = 0; t < kNc; ++t) {
+      if (kHostTab.e[t][AXIS] != e) continue;
+      double acc = q[t];
+      int u = t;
+#pragma unroll
+      for (int i = e - 1; i >= 0; --i) {
+        u = kHostTab.dm1[u][AXIS];
+        acc += (kHostTab.binom[e][i] * pw[e - i]) * q[u];
+      }
+      q[t] = acc;
+    }
+  }
+}
+template <int AXIS>
+GTAP_DEV void shift_locals(double *l, double s) {  // L'_v = sum_i C(i, v) s^(i - v) L_i
+  double pw[kP + 1];
+  pw[0] = 1.0;
+#pragma unroll
+  for (int i = 1; i <= kP; ++i) pw[i] = pw[i - 1] * s;
+#pragma unroll
+  for (int e = 0; e < kP; ++e) {  // ascending: the higher exponents are still the old ones
+#pragma unroll
+    for (int t = 0; t < kNc; ++t) {
+      if (kHostTab.e[t][AXIS] != e) continue;
+      double acc = l[t];
+#pragma unroll
+      for (int i = e + 1; i <= kP; ++i) {
+        const int d = kHostTab.deg[t] - e + i;
+        if (d > kP) continue;
+        const int u = kHostTab.idx[AXIS == 0 ? i : kHostTab.e[t][0]][AXIS == 1 ? i : kHostTab.e[t][1]]
+                                  [AXIS == 2 ? i : kHostTab.e[t][2]];
+        acc += (kHostTab.binom[i][e] * pw[i - e]) * l[u];
+      }
+      l[t] = acc;
+    }
+  }
 }
 
-// P2M for the leaves among cells [lo, hi): one workgroup of 128 per cell,
-// thread t < 84 owns moment t; the leaf's points are staged through LDS.
-__global__ __launch_bounds__(128) void k_p2m(const int32_t *cell, int32_t lo, int32_t hi, const double *px,
-                                             const double *py, const double *pz, const double *pq, double *Q) {
+// The 84 coefficients of one cell, 16 bytes at a time (rows are 672 bytes).
+GTAP_DEV void load_coefs(const double *src, double *v) {
+  const double2 *p = reinterpret_cast<const double2 *>(src);
+#pragma unroll
+  for (int t = 0; t < kNc / 2; ++t) {
+    const double2 x = p[t];
+    v[2 * t] = x.x;
+    v[2 * t + 1] = x.y;
+  }
+}
+
+// Sum over the 8 lanes of an aligned group, by DPP.
+template <int CTRL>
+GTAP_DEV double dpp_add(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint64_t y = dpp_in64<CTRL, 0xF>(b);
+  return x + __builtin_bit_cast(double, y);
+}
+GTAP_DEV double sum8(double x) {
+  x = dpp_add<0xB1>(x);   // lane ^ 1
+  x = dpp_add<0x4E>(x);   // lane ^ 2
+  return dpp_add<0x141>(x);  // lane ^ 7 (every quad already holds its sum)
+}
+
+// ---- upward pass ----------------------------------------------------------------
+// P2M for the leaves among cells [lo, hi): one wavefront per cell.  The powers
+// of 64 points' offsets go to LDS (one point per lane); lane t then sums the
+// monomials t and t + 64 over the points.
+__global__ __launch_bounds__(64) void k_p2m(const int32_t *cell, int32_t lo, int32_t hi, const double *px,
+                                            const double *py, const double *pz, const double *pq, double *Q) {
   const int32_t c = lo + static_cast<int32_t>(blockIdx.x);
   if (c >= hi) return;
   const int32_t *C = cell + static_cast<size_t>(c) * kCellInts;
   if (C[7] != 0) return;
-  __shared__ double sx[128], sy[128], sz[128], sq[128];
+  __shared__ double pw[3][kP + 1][kWave];
   const double cx = cell_centre(C[1], C[0]), cy = cell_centre(C[2], C[0]), cz = cell_centre(C[3], C[0]);
-  const int t = threadIdx.x;
-  double acc = 0.0;
-  const int ex = t < kNc ? kTab.e[t][0] : 0, ey = t < kNc ? kTab.e[t][1] : 0, ez = t < kNc ? kTab.e[t][2] : 0;
-  for (int32_t b = C[4]; b < C[5]; b += 128) {
+  const int t = threadIdx.x, t2 = t + 64 < kNc ? t + 64 : t;
+  const int e[2][3] = {{kTab.e[t][0], kTab.e[t][1], kTab.e[t][2]}, {kTab.e[t2][0], kTab.e[t2][1], kTab.e[t2][2]}};
+  double acc0 = 0.0, acc1 = 0.0;
+  for (int32_t b = C[4]; b < C[5]; b += static_cast<int32_t>(kWave)) {
     const int32_t k = b + t;
     if (k < C[5]) {
-      sx[t] = px[k] - cx;
-      sy[t] = py[k] - cy;
-      sz[t] = pz[k] - cz;
-      sq[t] = pq[k];
+      const double d[3] = {px[k] - cx, py[k] - cy, pz[k] - cz};
+      double x = pq[k], y = 1.0, z = 1.0;  // the charge travels with x
+#pragma unroll
+      for (int i = 0; i <= kP; ++i) {
+        pw[0][i][t] = x;
+        pw[1][i][t] = y;
+        pw[2][i][t] = z;
+        x *= d[0];
+        y *= d[1];
+        z *= d[2];
+      }
     }
     __syncthreads();
-    const int m = min(128, C[5] - b);
-    if (t < kNc)
-      for (int j = 0; j < m; ++j) {
-        double v = sq[j];
-        for (int i = 0; i < ex; ++i) v *= sx[j];
-        for (int i = 0; i < ey; ++i) v *= sy[j];
-        for (int i = 0; i < ez; ++i) v *= sz[j];
-        acc += v;
-      }
+    const int m = min(static_cast<int>(kWave), C[5] - b);
+    for (int j = 0; j < m; ++j) {
+      acc0 += pw[0][e[0][0]][j] * pw[1][e[0][1]][j] * pw[2][e[0][2]][j];
+      acc1 += pw[0][e[1][0]][j] * pw[1][e[1][1]][j] * pw[2][e[1][2]][j];
+    }
     __syncthreads();
   }
-  if (t < kNc) Q[static_cast<size_t>(c) * kNc + t] = acc;
+  Q[static_cast<size_t>(c) * kNc + t] = acc0;
+  if (t + 64 < kNc) Q[static_cast<size_t>(c) * kNc + t + 64] = acc1;
 }
 
-// M2M for the internal cells among [lo, hi) (children already final).
-__global__ __launch_bounds__(128) void k_m2m(const int32_t *cell, int32_t lo, int32_t hi, double *Q) {
-  const int32_t c = lo + static_cast<int32_t>(blockIdx.x);
-  if (c >= hi) return;
-  const int32_t *C = cell + static_cast<size_t>(c) * kCellInts;
-  if (C[7] == 0) return;
-  const int t = threadIdx.x;
-  if (t >= kNc) return;
-  const double cx = cell_centre(C[1], C[0]), cy = cell_centre(C[2], C[0]), cz = cell_centre(C[3], C[0]);
-  const int b0 = kTab.e[t][0], b1 = kTab.e[t][1], b2 = kTab.e[t][2];
-  double acc = 0.0;
-  for (int32_t k = 0; k < C[7]; ++k) {
-    const int32_t ch = C[6] + k;
-    const int32_t *D = cell + static_cast<size_t>(ch) * kCellInts;
-    double sx[kP + 1], sy[kP + 1], sz[kP + 1];
-    powers(cell_centre(D[1], D[0]) - cx, sx);
-    powers(cell_centre(D[2], D[0]) - cy, sy);
-    powers(cell_centre(D[3], D[0]) - cz, sz);
-    const double *Qc = Q + static_cast<size_t>(ch) * kNc;
-    for (int i = 0; i <= b0; ++i)
-      for (int j = 0; j <= b1; ++j)
-        for (int l = 0; l <= b2; ++l)
-          acc += kTab.binom[b0][i] * kTab.binom[b1][j] * kTab.binom[b2][l] * Qc[kTab.idx[i][j][l]] *
-                 sx[b0 - i] * sy[b1 - j] * sz[b2 - l];
+// M2M for the internal cells among [lo, hi) (children already final): eight
+// lanes per cell, a child on each, its moments re-centred in registers and
+// summed over the lanes.
+__global__ __launch_bounds__(256) void k_m2m(const int32_t *cell, int32_t lo, int32_t hi, double *Q) {
+  const int32_t g = static_cast<int32_t>((blockIdx.x * 256u + threadIdx.x) / 8);
+  const int32_t k = static_cast<int32_t>(threadIdx.x % 8);
+  const int32_t c = lo + g;
+  int32_t nch = 0, first = 0;
+  const int32_t *C = cell + static_cast<size_t>(c < hi ? c : lo) * kCellInts;
+  if (c < hi) {
+    nch = C[7];
+    first = C[6];
   }
-  Q[static_cast<size_t>(c) * kNc + t] = acc;
+  if (ballot(nch > 0) == 0ull) return;  // wave-uniform: the sums below need every lane
+  double q[kNc];
+#pragma unroll
+  for (int t = 0; t < kNc; ++t) q[t] = 0.0;
+  if (k < nch) {
+    const int32_t ch = first + k;
+    const int32_t *D = cell + static_cast<size_t>(ch) * kCellInts;
+    load_coefs(Q + static_cast<size_t>(ch) * kNc, q);
+    shift_moments<0>(q, cell_centre(D[1], D[0]) - cell_centre(C[1], C[0]));
+    shift_moments<1>(q, cell_centre(D[2], D[0]) - cell_centre(C[2], C[0]));
+    shift_moments<2>(q, cell_centre(D[3], D[0]) - cell_centre(C[3], C[0]));
+  }
+  double *dst = Q + static_cast<size_t>(c) * kNc;
+#pragma unroll
+  for (int t = 0; t < kNc; ++t) {
+    const double v = sum8(q[t]);
+    if (nch > 0 && k == (t & 7)) dst[t] = v;
+  }
 }
 
 // ---- downward pass --------------------------------------------------------------
-// L2L into the cells [lo, hi) from their parents (parents already final).
-__global__ __launch_bounds__(128) void k_l2l(const int32_t *cell, const int32_t *parent, int32_t lo, int32_t hi,
-                                             double *L) {
-  const int32_t c = lo + static_cast<int32_t>(blockIdx.x);
+// L2L into the cells [lo, hi) from their parents (parents already final): one
+// cell per lane, the parent's locals re-centred in registers.
+__global__ __launch_bounds__(64) void k_l2l(const int32_t *cell, const int32_t *parent, int32_t lo, int32_t hi,
+                                            double *L) {
+  const int32_t c = lo + static_cast<int32_t>(blockIdx.x * 64u + threadIdx.x);
   if (c >= hi) return;
-  const int t = threadIdx.x;
-  if (t >= kNc) return;
   const int32_t pc = parent[c];
   const int32_t *C = cell + static_cast<size_t>(c) * kCellInts;
   const int32_t *P = cell + static_cast<size_t>(pc) * kCellInts;
-  double sx[kP + 1], sy[kP + 1], sz[kP + 1];
-  powers(cell_centre(C[1], C[0]) - cell_centre(P[1], P[0]), sx);
-  powers(cell_centre(C[2], C[0]) - cell_centre(P[2], P[0]), sy);
-  powers(cell_centre(C[3], C[0]) - cell_centre(P[3], P[0]), sz);
-  const double *Lp = L + static_cast<size_t>(pc) * kNc;
-  const int v0 = kTab.e[t][0], v1 = kTab.e[t][1], v2 = kTab.e[t][2];
-  double acc = 0.0;
-  for (int u = 0; u < kNc; ++u) {
-    const int a0 = kTab.e[u][0], a1 = kTab.e[u][1], a2 = kTab.e[u][2];
-    if (a0 < v0 || a1 < v1 || a2 < v2) continue;
-    acc += kTab.binom[a0][v0] * kTab.binom[a1][v1] * kTab.binom[a2][v2] * Lp[u] * sx[a0 - v0] * sy[a1 - v1] *
-           sz[a2 - v2];
+  double l[kNc];
+  load_coefs(L + static_cast<size_t>(pc) * kNc, l);
+  shift_locals<0>(l, cell_centre(C[1], C[0]) - cell_centre(P[1], P[0]));
+  shift_locals<1>(l, cell_centre(C[2], C[0]) - cell_centre(P[2], P[0]));
+  shift_locals<2>(l, cell_centre(C[3], C[0]) - cell_centre(P[3], P[0]));
+  double2 *dst = reinterpret_cast<double2 *>(L + static_cast<size_t>(c) * kNc);
+#pragma unroll
+  for (int t = 0; t < kNc / 2; ++t) {
+    const double2 x = dst[t];
+    dst[t] = make_double2(x.x + l[2 * t], x.y + l[2 * t + 1]);
   }
-  L[static_cast<size_t>(c) * kNc + t] += acc;
 }
 
-// L2P for the leaves among [lo, hi): thread per point.
-__global__ __launch_bounds__(128) void k_l2p(const int32_t *cell, int32_t lo, int32_t hi, const double *L,
-                                             const double *px, const double *py, const double *pz, double *phi) {
+// L2P for the leaves among [lo, hi): one wavefront per leaf, a point per lane;
+// the leaf's coefficients are wave-uniform, nested in x, y, z.
+__global__ __launch_bounds__(64) void k_l2p(const int32_t *cell, int32_t lo, int32_t hi, const double *L,
+                                            const double *px, const double *py, const double *pz, double *phi) {
   const int32_t c = lo + static_cast<int32_t>(blockIdx.x);
   if (c >= hi) return;
   const int32_t *C = cell + static_cast<size_t>(c) * kCellInts;
   if (C[7] != 0) return;
-  __shared__ double sL[kNc];
-  if (threadIdx.x < kNc) sL[threadIdx.x] = L[static_cast<size_t>(c) * kNc + threadIdx.x];
-  __syncthreads();
+  const double *l = L + static_cast<size_t>(c) * kNc;
   const double cx = cell_centre(C[1], C[0]), cy = cell_centre(C[2], C[0]), cz = cell_centre(C[3], C[0]);
-  for (int32_t k = C[4] + static_cast<int32_t>(threadIdx.x); k < C[5]; k += blockDim.x) {
-    double sx[kP + 1], sy[kP + 1], sz[kP + 1];
-    powers(px[k] - cx, sx);
-    powers(py[k] - cy, sy);
-    powers(pz[k] - cz, sz);
-    double acc = 0.0;
-    for (int u = 0; u < kNc; ++u) acc += sL[u] * sx[kTab.e[u][0]] * sy[kTab.e[u][1]] * sz[kTab.e[u][2]];
-    phi[k] += acc;
+  for (int32_t k = C[4] + static_cast<int32_t>(threadIdx.x); k < C[5]; k += static_cast<int32_t>(kWave)) {
+    const double dx = px[k] - cx, dy = py[k] - cy, dz = pz[k] - cz;
+    double sx = 0.0;
+#pragma unroll
+    for (int i = kP; i >= 0; --i) {
+      double sy = 0.0;
+#pragma unroll
+      for (int j = kP - i; j >= 0; --j) {
+        double sz = 0.0;
+#pragma unroll
+        for (int m = kP - i - j; m >= 0; --m) sz = sz * dz + l[kHostTab.idx[i][j][m]];
+        sy = sy * dy + sz;
+      }
+      sx = sx * dx + sy;
+    }
+    phi[k] += sx;
   }
 }
 

@@ -755,10 +755,10 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
       !dev_alloc(&m.L, static_cast<size_t>(m.ncells) * fmm::kNc))
     return GTAP_E_NOMEM;
   if (hipMemsetAsync(m.L, 0, sizeof(double) * fmm::kNc * m.ncells, st) != hipSuccess) return GTAP_E_HIP;
-  hipLaunchKernelGGL(fmm::k_p2m, dim3(m.ncells), dim3(128), 0, st, m.cell, 0, m.ncells, px, py, pz, pq, m.Q);
+  hipLaunchKernelGGL(fmm::k_p2m, dim3(m.ncells), dim3(64), 0, st, m.cell, 0, m.ncells, px, py, pz, pq, m.Q);
   for (size_t l = m.levels.size(); l-- > 0;) {
     const auto [l0, l1] = m.levels[l];
-    hipLaunchKernelGGL(fmm::k_m2m, dim3(l1 - l0), dim3(128), 0, st, m.cell, l0, l1, m.Q);
+    hipLaunchKernelGGL(fmm::k_m2m, dim3(nblk(l1 - l0, 32)), dim3(256), 0, st, m.cell, l0, l1, m.Q);
   }
   if (hipEventRecord(m.ev[2], st) != hipSuccess) return GTAP_E_HIP;
   fmm::FmmDesc d{};
@@ -960,9 +960,9 @@ int fmm_finish(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m, float traversa
   if (hipEventRecord(m.ev[3], st) != hipSuccess) return GTAP_E_HIP;
   for (size_t l = 1; l < m.levels.size(); ++l) {
     const auto [l0, l1] = m.levels[l];
-    hipLaunchKernelGGL(fmm::k_l2l, dim3(l1 - l0), dim3(128), 0, st, m.cell, m.parent, l0, l1, m.L);
+    hipLaunchKernelGGL(fmm::k_l2l, dim3(nblk(l1 - l0, 64)), dim3(64), 0, st, m.cell, m.parent, l0, l1, m.L);
   }
-  hipLaunchKernelGGL(fmm::k_l2p, dim3(m.ncells), dim3(128), 0, st, m.cell, 0, m.ncells, m.L, px, py, pz, phi);
+  hipLaunchKernelGGL(fmm::k_l2p, dim3(m.ncells), dim3(64), 0, st, m.cell, 0, m.ncells, m.L, px, py, pz, phi);
   hipLaunchKernelGGL(fmm::k_scatter, dim3(nblk(n, 256)), dim3(256), 0, st, n, m.perm, phi, a.phi_dev);
   if (hipEventRecord(m.ev[4], st) != hipSuccess) return GTAP_E_HIP;
   fmm::FmmDesc d{};
