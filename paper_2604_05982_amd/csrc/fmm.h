@@ -13,7 +13,13 @@
 //   * Cartesian Taylor expansions of 1/|x - y| of total degree <= 6:
 //     moments Q_b = sum q (y - c_B)^b, locals
 //     L_a = sum_b C(a+b, a) (-1)^|b| T_{a+b}(c_A - c_B) Q_b, where T_g are the
-//     Taylor coefficients of 1/|d + h| from the Coulomb three-term recurrence.
+//     Taylor coefficients of 1/|d + h| from the Coulomb three-term recurrence;
+//   * M2L runs on reduced sets.  With T'_g = g! T_g, Q'_b = (-1)^|b| Q_b / b! and
+//     L'_a = a! L_a it is L'_a = sum_b T'_{a+b} Q'_b, and since 1/r is harmonic,
+//     T'_{g+2ez} = -T'_{g+2ex} - T'_{g+2ey}.  So moments with b_z >= 2 fold into
+//     those with b_z <= 1 (49 of 84), locals with a_z >= 2 follow from the
+//     others (both exactly, degree by degree), and the contraction has 532
+//     terms on 64 derivatives (g_z <= 2) instead of 924 on 84.
 #pragma once
 #include "layout.h"
 #include "wave.h"
@@ -30,7 +36,14 @@ constexpr int kCellInts = 8;                                   // level ax ay az
 
 // Number of coefficients of total degree <= d.
 constexpr int ncoef(int d) { return (d + 1) * (d + 2) * (d + 3) / 6; }
-constexpr int kM2LTerms = 924;  // pairs (a, b) with |a| + |b| <= 6
+constexpr int kNr = (kP + 1) * (kP + 1);  // 49 reduced coefficients (z exponent <= 1), 2 d + 1 of degree d
+constexpr int nred(int d) { return (d + 1) * (d + 1); }  // of degree <= d
+// Doubles between two cells' reduced moments: degrees <= 4 (25) from 0, degrees
+// 5 and 6 (24) from 26 -- two halves of thirteen 16-byte units.
+constexpr int kQrStride = 52;
+constexpr int qr_at(int r) { return r < nred(4) ? r : r + 1; }
+constexpr int kNg = kNr + (kP - 1) * kP / 2;  // 64 derivatives with z exponent <= 2: the reduced ones, then z = 2
+constexpr int kM2LTerms = 532;  // pairs (a, b) of reduced coefficients with |a| + |b| <= 6
 
 // Multi-index tables, generated at compile time.  Coefficients are ordered by
 // total degree, then by descending x and y exponents.
@@ -40,10 +53,14 @@ struct Tables {
   uint8_t deg[kNc];
   uint8_t dm1[kNc][3];                   // index of g - e_i (0xFF if g_i == 0)
   uint8_t dm2[kNc][3];                   // index of g - 2 e_i (0xFF if g_i < 2)
-  uint16_t m2l_first[kNc + 1];           // terms of target a: [m2l_first[a], m2l_first[a+1])
-  uint8_t m2l_b[kM2LTerms];              // source moment index b
-  uint8_t m2l_g[kM2LTerms];              // derivative index a + b
-  double m2l_c[kM2LTerms];               // C(a + b, a) (-1)^|b|
+  uint8_t red[kNr];                      // coefficient of reduced index r
+  uint8_t red_of[kNc];                   // inverse (0xFF: z exponent >= 2)
+  uint8_t g_of[kP + 1][kP + 1][3];       // index of derivative (x, y, z <= 2) among the 64
+  uint8_t ge[kNg][3];                    // its exponents
+  uint16_t m2l_first[kNr + 1];           // terms of reduced target a: [m2l_first[a], m2l_first[a+1])
+  uint8_t m2l_b[kM2LTerms];              // reduced source moment b
+  uint8_t m2l_g[kM2LTerms];              // derivative a + b
+  double fact[kNc];                      // e_x! e_y! e_z!
   double binom[2 * kP + 1][2 * kP + 1];
 };
 
@@ -79,31 +96,50 @@ constexpr Tables make_tables() {
         }
       }
     }
+  int r = 0;
+  for (int s = 0; s < kNc; ++s) {
+    double v = 1.0;
+    for (int i = 0; i < 3; ++i)
+      for (int k = 2; k <= T.e[s][i]; ++k) v *= k;
+    T.fact[s] = v;
+    T.red_of[s] = 0xFF;
+    if (T.e[s][2] <= 1) {
+      T.red[r] = static_cast<uint8_t>(s);
+      T.red_of[s] = static_cast<uint8_t>(r);
+      T.g_of[T.e[s][0]][T.e[s][1]][T.e[s][2]] = static_cast<uint8_t>(r);
+      for (int i = 0; i < 3; ++i) T.ge[r][i] = T.e[s][i];
+      ++r;
+    }
+  }
+  for (int s = 0; s < kNc; ++s)
+    if (T.e[s][2] == 2) {
+      T.g_of[T.e[s][0]][T.e[s][1]][2] = static_cast<uint8_t>(r);
+      for (int i = 0; i < 3; ++i) T.ge[r][i] = T.e[s][i];
+      ++r;
+    }
   int m = 0;
-  for (int a = 0; a < kNc; ++a) {
+  for (int a = 0; a < kNr; ++a) {
     T.m2l_first[a] = static_cast<uint16_t>(m);
-    const int da = T.deg[a];
-    for (int b = 0; b < ncoef(kP - da); ++b) {
-      const int g0 = T.e[a][0] + T.e[b][0], g1 = T.e[a][1] + T.e[b][1], g2 = T.e[a][2] + T.e[b][2];
+    const int ta = T.red[a];
+    for (int b = 0; b < nred(kP - T.deg[ta]); ++b) {
+      const int tb = T.red[b];
       T.m2l_b[m] = static_cast<uint8_t>(b);
-      T.m2l_g[m] = T.idx[g0][g1][g2];
-      const double c = T.binom[g0][T.e[a][0]] * T.binom[g1][T.e[a][1]] * T.binom[g2][T.e[a][2]];
-      T.m2l_c[m] = (T.deg[b] & 1) ? -c : c;
+      T.m2l_g[m] = T.g_of[T.e[ta][0] + T.e[tb][0]][T.e[ta][1] + T.e[tb][1]][T.e[ta][2] + T.e[tb][2]];
       ++m;
     }
   }
-  T.m2l_first[kNc] = static_cast<uint16_t>(m);
+  T.m2l_first[kNr] = static_cast<uint16_t>(m);
   return T;
 }
 
 __constant__ const Tables kTab = make_tables();
-static_assert(make_tables().m2l_first[kNc] == kM2LTerms, "M2L term count");
+static_assert(make_tables().m2l_first[kNr] == kM2LTerms, "M2L term count");
 
 // Per-job device descriptor of an FMM traversal.
 struct FmmDesc {
   const int32_t *cell;     // [ncells][kCellInts]
-  const double *Q;         // [ncells][kNc] multipole moments
-  double *L;               // [ncells][kNc] local coefficients (accumulated)
+  const double *Qr;        // [ncells][kQrStride] reduced moments
+  double *Lr;              // [ncells][kNr] reduced local coefficients (block mode accumulates them)
   const double *px, *py, *pz, *pq;  // points in sorted order
   double *phi;             // potentials in sorted order (accumulated)
   int64_t ta, tb;          // MAC theta = ta / tb
@@ -338,6 +374,46 @@ GTAP_DEV void load_coefs(const double *src, double *v) {
   }
 }
 
+// Reduced moments of every cell (see the top of the file), one cell per lane.
+__global__ __launch_bounds__(64) void k_reduce_moments(const double *Q, double *Qr, int32_t ncells) {
+  const int32_t c = static_cast<int32_t>(blockIdx.x * 64u + threadIdx.x);
+  if (c >= ncells) return;
+  double q[kNc];
+  load_coefs(Q + static_cast<size_t>(c) * kNc, q);
+#pragma unroll
+  for (int t = 0; t < kNc; ++t) q[t] *= ((kHostTab.deg[t] & 1) ? -1.0 : 1.0) / kHostTab.fact[t];
+#pragma unroll
+  for (int z = kP; z >= 2; --z) {
+#pragma unroll
+    for (int t = 0; t < kNc; ++t) {
+      if (kHostTab.e[t][2] != z) continue;
+      q[kHostTab.idx[kHostTab.e[t][0] + 2][kHostTab.e[t][1]][z - 2]] -= q[t];
+      q[kHostTab.idx[kHostTab.e[t][0]][kHostTab.e[t][1] + 2][z - 2]] -= q[t];
+    }
+  }
+  double *dst = Qr + static_cast<size_t>(c) * kQrStride;
+#pragma unroll
+  for (int r = 0; r < kNr; ++r) dst[qr_at(r)] = q[kHostTab.red[r]];
+}
+
+// Add a cell's local coefficients to l from its reduced ones.
+GTAP_DEV void add_reduced_locals(const double *src, double *l) {
+  double v[kNc];
+#pragma unroll
+  for (int r = 0; r < kNr; ++r) v[kHostTab.red[r]] = src[r];
+#pragma unroll
+  for (int z = 2; z <= kP; ++z) {
+#pragma unroll
+    for (int t = 0; t < kNc; ++t) {
+      if (kHostTab.e[t][2] != z) continue;
+      v[t] = -(v[kHostTab.idx[kHostTab.e[t][0] + 2][kHostTab.e[t][1]][z - 2]] +
+               v[kHostTab.idx[kHostTab.e[t][0]][kHostTab.e[t][1] + 2][z - 2]]);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < kNc; ++t) l[t] += v[t] * (1.0 / kHostTab.fact[t]);
+}
+
 // Sum over the 8 lanes of an aligned group, by DPP.
 template <int CTRL>
 GTAP_DEV double dpp_add(double x) {
@@ -427,26 +503,29 @@ __global__ __launch_bounds__(256) void k_m2m(const int32_t *cell, int32_t lo, in
 }
 
 // ---- downward pass --------------------------------------------------------------
-// L2L into the cells [lo, hi) from their parents (parents already final): one
-// cell per lane, the parent's locals re-centred in registers.
+// Local coefficients of the cells [lo, hi): M2L's sums (reduced) and, below the
+// root, L2L from the parents (already final), one cell per lane, re-centred
+// in registers.
 __global__ __launch_bounds__(64) void k_l2l(const int32_t *cell, const int32_t *parent, int32_t lo, int32_t hi,
-                                            double *L) {
+                                            const double *Lr, double *L) {
   const int32_t c = lo + static_cast<int32_t>(blockIdx.x * 64u + threadIdx.x);
   if (c >= hi) return;
   const int32_t pc = parent[c];
-  const int32_t *C = cell + static_cast<size_t>(c) * kCellInts;
-  const int32_t *P = cell + static_cast<size_t>(pc) * kCellInts;
   double l[kNc];
-  load_coefs(L + static_cast<size_t>(pc) * kNc, l);
-  shift_locals<0>(l, cell_centre(C[1], C[0]) - cell_centre(P[1], P[0]));
-  shift_locals<1>(l, cell_centre(C[2], C[0]) - cell_centre(P[2], P[0]));
-  shift_locals<2>(l, cell_centre(C[3], C[0]) - cell_centre(P[3], P[0]));
+#pragma unroll
+  for (int t = 0; t < kNc; ++t) l[t] = 0.0;
+  if (pc >= 0) {
+    const int32_t *C = cell + static_cast<size_t>(c) * kCellInts;
+    const int32_t *P = cell + static_cast<size_t>(pc) * kCellInts;
+    load_coefs(L + static_cast<size_t>(pc) * kNc, l);
+    shift_locals<0>(l, cell_centre(C[1], C[0]) - cell_centre(P[1], P[0]));
+    shift_locals<1>(l, cell_centre(C[2], C[0]) - cell_centre(P[2], P[0]));
+    shift_locals<2>(l, cell_centre(C[3], C[0]) - cell_centre(P[3], P[0]));
+  }
+  add_reduced_locals(Lr + static_cast<size_t>(c) * kNr, l);
   double2 *dst = reinterpret_cast<double2 *>(L + static_cast<size_t>(c) * kNc);
 #pragma unroll
-  for (int t = 0; t < kNc / 2; ++t) {
-    const double2 x = dst[t];
-    dst[t] = make_double2(x.x + l[2 * t], x.y + l[2 * t + 1]);
-  }
+  for (int t = 0; t < kNc / 2; ++t) dst[t] = make_double2(l[2 * t], l[2 * t + 1]);
 }
 
 // L2P for the leaves among [lo, hi): one wavefront per leaf, a point per lane;

@@ -237,13 +237,15 @@ __global__ __launch_bounds__(256) void k_list_hash(const uint64_t *pairs, uint64
   if (lane_id() == 0 && k) fetch_add_relaxed(count, k);
 }
 
-// 1 / sqrt(x) for x > 0: the hardware estimate refined by two Newton-Raphson
-// steps y <- y (3 - x y^2) / 2 (each squares the relative error).
-GTAP_DEV double rsqrt_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = y * (1.5 - 0.5 * x * y * y);
-  y = y * (1.5 - 0.5 * x * y * y);
-  return y;
+// 1 / sqrt(x) for x > 0: the hardware estimate y (relative error below 2^-23)
+// refined once with the third-order step y (1 + e / 2 + 3 e^2 / 8),
+// e = 1 - x y^2, whose error is of order e^3: the result is as close as two
+// Newton-Raphson steps leave it (both end in rounding), in five operations
+// instead of nine.
+GTAP_DEV double rsqrt_h(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-(x * y), y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
 }
 
 }  // namespace fmm

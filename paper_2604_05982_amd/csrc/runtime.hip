@@ -625,7 +625,8 @@ struct FmmJobMem {
   int32_t *cell = nullptr, *parent = nullptr;
   int64_t cell_cap = 0;
   int32_t *scratch = nullptr;  // nch | off | bnd | flags
-  double *Q = nullptr, *L = nullptr;
+  double *Q = nullptr, *L = nullptr;    // full moments and locals
+  double *Qr = nullptr, *Lr = nullptr;  // reduced ones, which M2L reads and writes
   fmm::FmmDesc *desc = nullptr;
   std::vector<std::pair<int32_t, int32_t>> levels;
   int32_t ncells = 0;
@@ -645,7 +646,7 @@ struct FmmJobMem {
 
 void fmm_free(FmmJobMem &m) {
   void *ptrs[] = {m.keys, m.keys_sorted, m.idx, m.perm, m.sort_tmp, m.pts, m.cell, m.parent, m.scratch,
-                  m.Q, m.L, m.desc, m.m2l, m.p2p, m.front, m.seg, m.sorted, m.lsort_tmp};
+                  m.Q, m.L, m.Qr, m.Lr, m.desc, m.m2l, m.p2p, m.front, m.seg, m.sorted, m.lsort_tmp};
   for (void *q : ptrs)
     if (q) (void)hipFree(q);
   for (hipEvent_t &e : m.ev)
@@ -661,6 +662,9 @@ bool dev_alloc(T **p, size_t count) {
 }
 
 unsigned nblk(int64_t n, unsigned b) { return static_cast<unsigned>(std::max<int64_t>((n + b - 1) / b, 1)); }
+
+// Workgroups of a grid of n positions in runs of `run` per XCD (fmm::xcd_position).
+unsigned xcd_grid(int64_t n, unsigned run) { return nblk(n, fmm::kXcds * run) * fmm::kXcds * run; }
 
 // Interaction-list capacities: the caller's, else an estimate from the number
 // of cells and theta (100 M2L and 30 P2P pairs per cell at theta = 1, growing
@@ -752,19 +756,24 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
   m.ncells = hi;
   if (hipEventRecord(m.ev[1], st) != hipSuccess) return GTAP_E_HIP;
   if (!dev_alloc(&m.Q, static_cast<size_t>(m.ncells) * fmm::kNc) ||
-      !dev_alloc(&m.L, static_cast<size_t>(m.ncells) * fmm::kNc))
+      !dev_alloc(&m.L, static_cast<size_t>(m.ncells) * fmm::kNc) ||
+      !dev_alloc(&m.Qr, static_cast<size_t>(m.ncells) * fmm::kQrStride) ||
+      !dev_alloc(&m.Lr, static_cast<size_t>(m.ncells) * fmm::kNr))
     return GTAP_E_NOMEM;
-  if (hipMemsetAsync(m.L, 0, sizeof(double) * fmm::kNc * m.ncells, st) != hipSuccess) return GTAP_E_HIP;
+  if (a.traversal == GTAP_FMM_TASKS &&  // the list evaluation writes every cell's
+      hipMemsetAsync(m.Lr, 0, sizeof(double) * fmm::kNr * m.ncells, st) != hipSuccess)
+    return GTAP_E_HIP;
   hipLaunchKernelGGL(fmm::k_p2m, dim3(m.ncells), dim3(64), 0, st, m.cell, 0, m.ncells, px, py, pz, pq, m.Q);
   for (size_t l = m.levels.size(); l-- > 0;) {
     const auto [l0, l1] = m.levels[l];
     hipLaunchKernelGGL(fmm::k_m2m, dim3(nblk(l1 - l0, 32)), dim3(256), 0, st, m.cell, l0, l1, m.Q);
   }
+  hipLaunchKernelGGL(fmm::k_reduce_moments, dim3(nblk(m.ncells, 64)), dim3(64), 0, st, m.Q, m.Qr, m.ncells);
   if (hipEventRecord(m.ev[2], st) != hipSuccess) return GTAP_E_HIP;
   fmm::FmmDesc d{};
   d.cell = m.cell;
-  d.Q = m.Q;
-  d.L = m.L;
+  d.Qr = m.Qr;
+  d.Lr = m.Lr;
   d.px = px;
   d.py = py;
   d.pz = pz;
@@ -929,14 +938,12 @@ int fmm_eval_lists(gtap_ctx *c, FmmJobMem &m, uint64_t n_m2l, uint64_t n_p2p, gt
   if (hipEventRecord(m.lev[2], st) != hipSuccess) return GTAP_E_HIP;
   if ((rc = prepare(m.m2l, n_m2l, &D->m2l_hash, &D->m2l_pairs))) return rc;
   if (hipEventRecord(m.lev[3], st) != hipSuccess) return GTAP_E_HIP;
-  hipLaunchKernelGGL(fmm::k_scale_moments, dim3(nblk(static_cast<int64_t>(m.ncells) * fmm::kNc, 256)), dim3(256), 0,
-                     st, m.Q, static_cast<int64_t>(m.ncells));
-  hipLaunchKernelGGL(fmm::k_m2l_list, dim3(m.ncells), dim3(fmm::kM2LThreads), 0, st, m.hdesc.cell, m.hdesc.Q,
-                     m.hdesc.L, m.sorted, lo, hi);
+  hipLaunchKernelGGL(fmm::k_m2l_list, dim3(xcd_grid(m.ncells, fmm::kM2LRun)), dim3(fmm::kM2LThreads), 0, st, m.hdesc.cell, m.hdesc.Qr,
+                     m.hdesc.Lr, m.sorted, lo, hi, static_cast<uint32_t>(m.ncells));
   if (hipEventRecord(m.lev[4], st) != hipSuccess) return GTAP_E_HIP;
   if ((rc = prepare(m.p2p, n_p2p, &D->p2p_hash, &D->p2p_pairs))) return rc;
   if (hipEventRecord(m.lev[5], st) != hipSuccess) return GTAP_E_HIP;
-  hipLaunchKernelGGL(fmm::k_p2p_list, dim3(nblk(static_cast<int64_t>((n_p2p + kWave - 1) / kWave), fmm::kP2PThreads / kWave)),
+  hipLaunchKernelGGL(fmm::k_p2p_list, dim3(xcd_grid(nblk(static_cast<int64_t>((n_p2p + kWave - 1) / kWave), fmm::kP2PThreads / kWave), fmm::kP2PRun)),
                      dim3(fmm::kP2PThreads), 0, st, m.hdesc.cell, m.hdesc.px, m.hdesc.py, m.hdesc.pz, m.hdesc.pq,
                      m.hdesc.phi, m.sorted, n_p2p, static_cast<uint32_t>(m.ncells), &D->p2p_inter, &D->coincident);
   if (hipEventRecord(m.lev[6], st) != hipSuccess) return GTAP_E_HIP;
@@ -958,9 +965,8 @@ int fmm_finish(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m, float traversa
   const int32_t n = a.n;
   double *px = m.pts, *py = px + n, *pz = py + n, *phi = pz + 2 * static_cast<size_t>(n);
   if (hipEventRecord(m.ev[3], st) != hipSuccess) return GTAP_E_HIP;
-  for (size_t l = 1; l < m.levels.size(); ++l) {
-    const auto [l0, l1] = m.levels[l];
-    hipLaunchKernelGGL(fmm::k_l2l, dim3(nblk(l1 - l0, 64)), dim3(64), 0, st, m.cell, m.parent, l0, l1, m.L);
+  for (const auto &[l0, l1] : m.levels) {
+    hipLaunchKernelGGL(fmm::k_l2l, dim3(nblk(l1 - l0, 64)), dim3(64), 0, st, m.cell, m.parent, l0, l1, m.Lr, m.L);
   }
   hipLaunchKernelGGL(fmm::k_l2p, dim3(m.ncells), dim3(64), 0, st, m.cell, 0, m.ncells, m.L, px, py, pz, phi);
   hipLaunchKernelGGL(fmm::k_scatter, dim3(nblk(n, 256)), dim3(256), 0, st, n, m.perm, phi, a.phi_dev);

@@ -45,7 +45,7 @@ constexpr uint32_t kMaxBlockThreads = 256;
 constexpr uint32_t kBlockStackSmall = 2 * kChunkSmall;
 constexpr uint32_t kP2PTile = 64;
 constexpr uint32_t kBlkLocal = 128;  // private stack of cell-pair task images
-constexpr uint32_t kM2LSlots = 1024; // >= ceil(924 / threads) * threads for 64, 128, 256 threads
+constexpr uint32_t kM2LSlots = 768;  // >= ceil(532 / threads) * threads for 64, 128, 256 threads
 
 struct BlockLds {
   uint32_t stk_s[kBlockStackSmall];
@@ -68,26 +68,26 @@ struct BlockLds {
   uint32_t first_fail;          // UTS: first failed draw in a batch
   int64_t bottom, top_seen;     // owner's view of its deque
   union {                       // the M2L batch completes before the P2P batch starts
-    double Tc[8][fmm::kNc];     // Taylor coefficients of the batch's M2L pairs
+    double Tc[8][fmm::kNg];     // derivatives of the batch's M2L pairs
     double red[kMaxBlockThreads];  // P2P: partial sums of the source groups
-    double pstage[8 * fmm::kNc];   // P2P: [kMaxBlockThreads, +256) staged source chunks
+    double pstage[8 * fmm::kNg];   // P2P: [kMaxBlockThreads, +256) staged source chunks
   };
-  double QBc[8][fmm::kNc];      // source moments of the M2L pairs
+  double QBc[8][fmm::kNr];      // reduced source moments of the M2L pairs
   double dl[8][4];              // M2L pair i: centre difference A - B and the reciprocal of its squared length
-  uint32_t dmt[fmm::kNc][2];    // Taylor recursion indices of coefficient t: g - e_c (byte c of [0]), g - 2 e_c ([1])
+  // derivative recursion of index g < 49: g - e_c (byte c of [0]), g - 2 e_c ([1]; 0xFF: none), exponents ([2]);
+  // from 49 on (z = 2): the two indices that it is minus the sum of
+  uint32_t dmt[fmm::kNg][3];
   uint4 lstk[2 * kBlkLocal];    // private stack (frame words 0..7 of each task)
   uint32_t lbot, ltop, local, dry;
-  // M2L term table, copied once per workgroup:
-  // a | b << 8 | (a+b) << 16 | coefficient << 24 (the coefficient
-  // C(a+b, a) (-1)^|b| is an integer of magnitude <= 20, kept as int8).
-  // Thread t owns the consecutive terms [t*C, (t+1)*C) (C = ceil(924 /
+  // M2L term table, copied once per workgroup: a | b << 8 | (a+b) << 16.
+  // Thread t owns the consecutive terms [t*C, (t+1)*C) (C = ceil(532 /
   // threads)); its r-th term is stored at r * threads + t so that a round of
   // loads touches consecutive words.
   uint32_t mab[kM2LSlots];
   // Running sums for the target cell of consecutive pairs (siblings of one
   // split share it): M2L local coefficients of cell lcell, P2P potentials of
   // the points of leaf pcell.  Added to memory when the target changes.
-  double lacc[fmm::kNc];
+  double lacc[fmm::kNr];
   double pacc[kP2PTile];
   const fmm::FmmDesc *ldesc;
   const fmm::FmmDesc *pdesc;
@@ -100,8 +100,8 @@ template <int NT>
 GTAP_DEV void fmm_flush_acc(BlockLds &S, bool m2l, bool p2p) {
   const uint32_t tx = threadIdx.x;
   if (m2l && S.lcell != kNone) {
-    for (uint32_t t = tx; t < static_cast<uint32_t>(fmm::kNc); t += NT) {
-      unsafeAtomicAdd(S.ldesc->L + static_cast<size_t>(S.lcell) * fmm::kNc + t, S.lacc[t]);
+    for (uint32_t t = tx; t < static_cast<uint32_t>(fmm::kNr); t += NT) {
+      unsafeAtomicAdd(S.ldesc->Lr + static_cast<size_t>(S.lcell) * fmm::kNr + t, S.lacc[t]);
       S.lacc[t] = 0.0;
     }
   }
@@ -205,16 +205,6 @@ GTAP_DEV double lane_double(double x, int32_t k) {
   return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-constexpr bool m2l_coefficients_fit_int8() {
-  const fmm::Tables T = fmm::make_tables();
-  for (int m = 0; m < fmm::kM2LTerms; ++m) {
-    const double c = T.m2l_c[m];
-    if (c != static_cast<double>(static_cast<int32_t>(c)) || c > 127.0 || c < -127.0) return false;
-  }
-  return true;
-}
-static_assert(m2l_coefficients_fit_int8(), "the M2L term table packs its coefficients as int8");
-
 // Branch of the pair of cell records (A, B): 1 accept (M2L), 2 both leaves
 // (P2P), 0 split.
 GTAP_DEV uint32_t fmm_branch(const int32_t *A, const int32_t *B, const FmmCounters &fc) {
@@ -236,8 +226,8 @@ GTAP_DEV void fmm_target(BlockLds &S, const fmm::FmmDesc *D, uint32_t a, bool m2
   const uint32_t tx = threadIdx.x;
   if (m2l) {
     if (S.lcell != kNone) {
-      for (uint32_t t = tx; t < static_cast<uint32_t>(fmm::kNc); t += NT) {
-        unsafeAtomicAdd(S.ldesc->L + static_cast<size_t>(S.lcell) * fmm::kNc + t, S.lacc[t]);
+      for (uint32_t t = tx; t < static_cast<uint32_t>(fmm::kNr); t += NT) {
+        unsafeAtomicAdd(S.ldesc->Lr + static_cast<size_t>(S.lcell) * fmm::kNr + t, S.lacc[t]);
         S.lacc[t] = 0.0;
       }
     }
@@ -261,9 +251,9 @@ GTAP_DEV void fmm_target(BlockLds &S, const fmm::FmmDesc *D, uint32_t a, bool m2
   }
 }
 
-// M2L(A <- B) for the batch's pairs m2l_idx[0 .. n): Taylor coefficients of
-// 1/|d + h| degree by degree for all of them at once, then each pair's 924
-// terms spread evenly over the workgroup into the running sums of its target.
+// M2L(A <- B) for the batch's pairs m2l_idx[0 .. n): the derivatives of 1/|d|
+// degree by degree for all of them at once, then each pair's 532 terms spread
+// evenly over the workgroup into the running (reduced) sums of its target.
 constexpr double kInvDeg[fmm::kP + 1] = {0.0, 1.0, 1.0 / 2, 1.0 / 3, 1.0 / 4, 1.0 / 5, 1.0 / 6};
 static_assert(fmm::kP == 6, "reciprocal table of the Taylor degrees");
 
@@ -280,9 +270,9 @@ GTAP_DEV void fmm_m2l_batch(const Params &p, BlockLds &S, const fmm::FmmDesc *D,
     d2 = fmm::cell_centre(A[3], A[0]) - fmm::cell_centre(B[3], B[0]);
   };
   // source moments of every pair (one round of loads), and T_0
-  for (uint32_t x = tx; x < n * static_cast<uint32_t>(fmm::kNc); x += NT) {
-    const uint32_t i = x / fmm::kNc, t = x - i * fmm::kNc;
-    S.QBc[i][t] = D->Q[static_cast<size_t>(S.pid[S.m2l_idx[i]][1]) * fmm::kNc + t];
+  for (uint32_t x = tx; x < n * static_cast<uint32_t>(fmm::kNr); x += NT) {
+    const uint32_t i = x / fmm::kNr, t = x - i * fmm::kNr;
+    S.QBc[i][t] = D->Qr[static_cast<size_t>(S.pid[S.m2l_idx[i]][1]) * fmm::kQrStride + fmm::qr_at(static_cast<int>(t))];
   }
   if (tx < n) {
     double d0, d1, d2;
@@ -304,21 +294,27 @@ GTAP_DEV void fmm_m2l_batch(const Params &p, BlockLds &S, const fmm::FmmDesc *D,
     const uint32_t wv = tx / kWave, ln = tx % kWave;
     const uint32_t nw = n > wv ? (n - wv + G - 1) / G : 0u;
     for (int deg = 1; deg <= fmm::kP; ++deg) {
-      const uint32_t lo = static_cast<uint32_t>(fmm::ncoef(deg - 1)), nd = static_cast<uint32_t>(fmm::ncoef(deg)) - lo;
+      const uint32_t lo = static_cast<uint32_t>(fmm::nred(deg - 1)), nd = static_cast<uint32_t>(2 * deg + 1);
       for (uint32_t x = ln; x < nw * nd; x += kWave) {
         const uint32_t ii = x / nd, t = lo + (x - ii * nd);
         const uint32_t i = wv + ii * G;
-        const uint32_t m1w = S.dmt[t][0], m2w = S.dmt[t][1];
+        const uint32_t m1w = S.dmt[t][0], m2w = S.dmt[t][1], ew = S.dmt[t][2];
         double s1 = 0.0, s2 = 0.0;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const uint32_t m1 = (m1w >> (8 * c)) & 0xFFu, m2 = (m2w >> (8 * c)) & 0xFFu;
-          if (m1 != 0xFFu) s1 += S.dl[i][c] * S.Tc[i][m1];
-          if (m2 != 0xFFu) s2 += S.Tc[i][m2];
+          const uint32_t m1 = (m1w >> (8 * c)) & 0xFFu, m2 = (m2w >> (8 * c)) & 0xFFu, e = (ew >> (8 * c)) & 0xFFu;
+          if (m1 != 0xFFu) s1 += static_cast<double>(e) * S.dl[i][c] * S.Tc[i][m1];
+          if (m2 != 0xFFu) s2 += static_cast<double>(e * (e - 1)) * S.Tc[i][m2];
         }
         S.Tc[i][t] = -((2.0 * deg - 1.0) * s1 + (deg - 1.0) * s2) * (S.dl[i][3] * kInvDeg[deg]);
       }
       wave_sync();
+    }
+    constexpr uint32_t N2 = static_cast<uint32_t>(fmm::kNg - fmm::kNr);
+    for (uint32_t x = ln; x < nw * N2; x += kWave) {
+      const uint32_t ii = x / N2, t = static_cast<uint32_t>(fmm::kNr) + (x - ii * N2);
+      const uint32_t i = wv + ii * G;
+      S.Tc[i][t] = -(S.Tc[i][S.dmt[t][0]] + S.Tc[i][S.dmt[t][1]]);
     }
   }
   __syncthreads();
@@ -346,7 +342,7 @@ GTAP_DEV void fmm_m2l_batch(const Params &p, BlockLds &S, const fmm::FmmDesc *D,
         const uint32_t g = (w >> 16) & 0xFFu, bq = (w >> 8) & 0xFFu;
         double sum = 0.0;
         for (uint32_t q = i; q < j; ++q) sum += S.Tc[q][g] * S.QBc[q][bq];
-        acc += static_cast<double>(static_cast<int8_t>(w >> 24)) * sum;
+        acc += sum;
       }
     }
     if (cur != 0xFFu) atomicAdd(&S.lacc[cur], acc);
@@ -452,7 +448,7 @@ GTAP_DEV void fmm_p2p_batch(BlockLds &S, const fmm::FmmDesc *D, FmmCounters &fc)
     // each wavefront's chunk, staged in LDS behind the reduction slots (the
     // M2L coefficients' space, free during P2P) and read back by all lanes
     // from one address per source
-    static_assert(kMaxBlockThreads + kWave * 4 <= 8 * fmm::kNc, "P2P staging space");
+    static_assert(kMaxBlockThreads + kWave * 4 <= 8 * fmm::kNg, "P2P staging space");
     double *const stage = S.pstage + kMaxBlockThreads + static_cast<uint32_t>(wsrc) * static_cast<uint32_t>(SC) * 4u;
     for (int32_t c0 = wsrc * SC; c0 < stotal; c0 += static_cast<int32_t>(G) * SC) {
       // this lane's source of the chunk: the (c0 + lane)-th of the concatenated ranges
@@ -485,7 +481,7 @@ GTAP_DEV void fmm_p2p_batch(BlockLds &S, const fmm::FmmDesc *D, FmmCounters &fc)
         if (r2 == 0.0) {
           if (live && __builtin_amdgcn_readlane(sj, k) != i) ++coinc;
         } else {
-          acc += s1.y * fmm::rsqrt_nr(r2);
+          acc += s1.y * fmm::rsqrt_h(r2);
         }
       }
       wave_sync();  // the chunk's reads are issued before the next chunk overwrites it
@@ -649,17 +645,25 @@ __global__ __launch_bounds__(NT) void block_sched_kernel(Params p) {
       if (m < static_cast<uint32_t>(fmm::kM2LTerms)) {
         uint32_t at = 0;
         while (fmm::kTab.m2l_first[at + 1] <= m) ++at;
-        const int32_t c = static_cast<int32_t>(fmm::kTab.m2l_c[m]);
-        w = at | (static_cast<uint32_t>(fmm::kTab.m2l_b[m]) << 8) | (static_cast<uint32_t>(fmm::kTab.m2l_g[m]) << 16) |
-            (static_cast<uint32_t>(static_cast<uint8_t>(static_cast<int8_t>(c))) << 24);
+        w = at | (static_cast<uint32_t>(fmm::kTab.m2l_b[m]) << 8) | (static_cast<uint32_t>(fmm::kTab.m2l_g[m]) << 16);
       }
       S.mab[r * NT + tx] = w;
     }
   }
-  for (uint32_t t = tx; t < static_cast<uint32_t>(fmm::kNc); t += NT) {
-    S.lacc[t] = 0.0;
-    S.dmt[t][0] = fmm::kTab.dm1[t][0] | (fmm::kTab.dm1[t][1] << 8) | (fmm::kTab.dm1[t][2] << 16);
-    S.dmt[t][1] = fmm::kTab.dm2[t][0] | (fmm::kTab.dm2[t][1] << 8) | (fmm::kTab.dm2[t][2] << 16);
+  for (uint32_t t = tx; t < static_cast<uint32_t>(fmm::kNr); t += NT) S.lacc[t] = 0.0;
+  for (uint32_t t = tx; t < static_cast<uint32_t>(fmm::kNg); t += NT) {
+    const uint32_t x = fmm::kTab.ge[t][0], y = fmm::kTab.ge[t][1], z = fmm::kTab.ge[t][2];
+    auto g_of = [&](uint32_t i, uint32_t j, uint32_t k) { return static_cast<uint32_t>(fmm::kTab.g_of[i][j][k]); };
+    if (t < static_cast<uint32_t>(fmm::kNr)) {
+      S.dmt[t][0] = (x >= 1 ? g_of(x - 1, y, z) : 0xFFu) | ((y >= 1 ? g_of(x, y - 1, z) : 0xFFu) << 8) |
+                    ((z >= 1 ? g_of(x, y, z - 1) : 0xFFu) << 16);
+      S.dmt[t][1] = (x >= 2 ? g_of(x - 2, y, z) : 0xFFu) | ((y >= 2 ? g_of(x, y - 2, z) : 0xFFu) << 8) | (0xFFu << 16);
+      S.dmt[t][2] = x | (y << 8) | (z << 16);
+    } else {
+      S.dmt[t][0] = g_of(x + 2, y, 0);
+      S.dmt[t][1] = g_of(x, y + 2, 0);
+      S.dmt[t][2] = 0;
+    }
   }
   for (uint32_t t = tx; t < kP2PTile; t += NT) S.pacc[t] = 0.0;
   if (tx == 0) {
