@@ -230,9 +230,10 @@ __global__ void k_root(int32_t *cell, int32_t *parent, int32_t n) {
 }
 
 // Cells [lo, hi) of one level: octant boundaries of each splitting cell by
-// binary search in its sorted key range, and the number of non-empty children.
+// binary search in its sorted key range, and the number of non-empty children;
+// *nsplit counts the cells that split.
 __global__ void k_level_count(int32_t *cell, int32_t lo, int32_t hi, const uint64_t *keys, int32_t leaf_max,
-                              int32_t *nch, int32_t *bnd) {
+                              int32_t *nch, int32_t *bnd, int32_t *nsplit) {
   const int32_t c = lo + static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
   if (c >= hi) return;
   const int32_t *C = cell + static_cast<size_t>(c) * kCellInts;
@@ -253,6 +254,8 @@ __global__ void k_level_count(int32_t *cell, int32_t lo, int32_t hi, const uint6
     }
     B[8] = e;
     for (int oct = 0; oct < 8; ++oct) cnt += (B[oct + 1] > B[oct]) ? 1 : 0;
+    const uint64_t m = ballot(true);  // the lanes whose cells split
+    if (static_cast<int>(lane_id()) == __builtin_ctzll(m)) atomicAdd(nsplit, __popcll(m));
   }
   nch[c - lo] = cnt;
 }

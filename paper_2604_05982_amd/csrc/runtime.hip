@@ -241,6 +241,118 @@ int fill_params(const gtap_config &cfg, uint32_t nw, const Layout &L, char *ws, 
   return rate_khz;
 }
 
+// Device buffers a context keeps between runs for the jobs that need memory of
+// their own (FMM trees and lists, split k-clique matrices): allocating and
+// freeing them in every run took 2 to 5 ms (hipFree waits for the device), as
+// long as everything else around the kernels of a 10^5-point FMM job.  A run
+// takes the smallest unused buffer that fits and is at most twice as large;
+// what is unused at its end beyond kCacheBytes goes back to the device, the
+// rest with the context.  Reuse is safe because a context belongs to one host
+// thread and a run ends only when its stream is idle.
+constexpr size_t kCacheBytes = 8ull << 30;
+
+struct DevCache {
+  struct Buf {
+    void *p;
+    size_t bytes;
+    bool used;
+  };
+  std::vector<Buf> bufs;
+
+  void *get(size_t bytes) {
+    bytes = align_up(bytes ? bytes : 1, 65536);
+    Buf *best = nullptr;
+    for (Buf &b : bufs)
+      if (!b.used && b.bytes >= bytes && b.bytes <= 2 * bytes + (1u << 20) && (!best || b.bytes < best->bytes)) best = &b;
+    if (best) {
+      best->used = true;
+      return best->p;
+    }
+    try {
+      bufs.reserve(bufs.size() + 1);
+    } catch (...) {
+      return nullptr;
+    }
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      trim(0);  // unused buffers first
+      if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    }
+    bufs.push_back(Buf{p, bytes, true});
+    return p;
+  }
+  void put(const void *p) {
+    for (Buf &b : bufs)
+      if (b.p == p) b.used = false;
+  }
+  // Free unused buffers, largest first, until at most `keep` bytes are unused.
+  void trim(size_t keep) {
+    for (;;) {
+      size_t total = 0, at = 0;
+      for (size_t i = 0; i < bufs.size(); ++i) {
+        if (bufs[i].used) continue;
+        total += bufs[i].bytes;
+        if (bufs[at].used || bufs[i].bytes > bufs[at].bytes) at = i;
+      }
+      if (total <= keep) return;
+      (void)hipFree(bufs[at].p);
+      bufs.erase(bufs.begin() + static_cast<std::ptrdiff_t>(at));
+    }
+  }
+  void clear() {
+    for (Buf &b : bufs) (void)hipFree(b.p);
+    bufs.clear();
+  }
+};
+
+// Timing events kept by a context (a run takes as many as its jobs need).
+struct EventPool {
+  std::vector<hipEvent_t> free_ev;
+  hipEvent_t get() {
+    hipEvent_t e = nullptr;
+    if (!free_ev.empty()) {
+      e = free_ev.back();
+      free_ev.pop_back();
+    } else if (hipEventCreate(&e) != hipSuccess) {
+      return nullptr;
+    }
+    return e;
+  }
+  void put(hipEvent_t e) {
+    try {
+      if (free_ev.size() < 64) {
+        free_ev.push_back(e);
+        return;
+      }
+    } catch (...) {
+    }
+    (void)hipEventDestroy(e);
+  }
+  void clear() {
+    for (hipEvent_t e : free_ev) (void)hipEventDestroy(e);
+    free_ev.clear();
+  }
+};
+
+// Bit matrices of a split k-clique job: matrix words before each group of
+// kKsGroup vertices (device, from the context's cache; nullptr: no matrices)
+// and in all.
+struct KsPlan {
+  uint64_t *sums;
+  uint64_t words;
+};
+
+// Pinned host memory of a context for the small copies of a run (sizes read
+// back during tree construction, counters, the control block); the job table
+// of up to kPinnedJobs jobs goes through it too.
+constexpr size_t kPinnedJobs = 16;
+struct Pinned {
+  int64_t words[16];
+  Control ctl;
+  fmm::FmmDesc desc;
+  JobSlot jobs[kPinnedJobs];
+};
+
 }  // namespace
 
 struct gtap_ctx {
@@ -269,9 +381,10 @@ struct gtap_ctx {
   // FMM jobs: arguments by pending position, results by run position
   std::vector<gtap_fmm_args> pending_fmm;
   std::vector<gtap_fmm_result> done_fmm;
-  // split k-clique jobs: per pending job, each vertex's offset (in 64-bit
-  // words) into the job's bit-matrix buffer, n+1 entries (empty: no matrices)
-  std::vector<std::vector<uint64_t>> pending_ks;
+  std::vector<KsPlan> pending_ks;  // split k-clique jobs: their matrices, by pending position
+  DevCache cache;
+  EventPool events;
+  Pinned *pin = nullptr;
   gtap_stats stats{};
   gtap_error_report err{};
 };
@@ -342,7 +455,8 @@ int gtap_init(const gtap_config *cfg, gtap_ctx **out) {
     }
     c->owns_ws = true;
   }
-  if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) {
+  if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void **>(&c->pin), sizeof(Pinned), 0) != hipSuccess) {
     gtap_finalize(c);
     return GTAP_E_HIP;
   }
@@ -363,8 +477,7 @@ extern "C" int32_t gtap_kclique_split_buffer_ints(int32_t max_outdeg) {
 }
 
 // Validate a root task's arguments and pack them into a job slot.
-static int pack_job(const gtap_config &cfg, hipStream_t stream, int32_t kind, const void *args,
-                    size_t args_bytes, JobSlot &J, std::vector<uint64_t> *ks_off = nullptr) {
+static int pack_job(const gtap_config &cfg, int32_t kind, const void *args, size_t args_bytes, JobSlot &J) {
   if (!args) return GTAP_E_INVAL;
   std::memset(&J, 0, sizeof(J));
   J.kind = static_cast<uint32_t>(kind);
@@ -433,28 +546,6 @@ static int pack_job(const gtap_config &cfg, hipStream_t stream, int32_t kind, co
       if (a.k >= 4 && (cfg.big_frames == 0 ||
                        kcs::buffer_ints(static_cast<uint32_t>(a.max_outdeg)) > cfg.big_frame_ints))
         return GTAP_E_INVAL;
-      // the frame buffers are sized from max_outdeg: check it against the graph
-      if (a.n > 0) {
-        std::vector<int32_t> rp(static_cast<size_t>(a.n) + 1);
-        if (hipMemcpyAsync(rp.data(), a.row_ptr_dev, rp.size() * sizeof(int32_t), hipMemcpyDeviceToHost,
-                           stream) != hipSuccess ||
-            hipStreamSynchronize(stream) != hipSuccess)
-          return GTAP_E_HIP;
-        for (int32_t v = 0; v < a.n; ++v)
-          if (rp[v + 1] < rp[v] || rp[v + 1] - rp[v] > a.max_outdeg) return GTAP_E_INVAL;
-        // k >= 4: a vertex that forks row tasks (at least k-1 and more than
-        // threshold out-neighbours; smaller ones count in place) gets its
-        // d x W bit matrix (two of them for pivoting) in the job's buffer
-        if (ks_off && a.k >= 4) {
-          ks_off->assign(static_cast<size_t>(a.n) + 1, 0);
-          const uint64_t mats = a.algorithm == GTAP_KCLIQUE_PIVOT ? 2 : 1;
-          for (int32_t v = 0; v < a.n; ++v) {
-            const uint64_t d = static_cast<uint64_t>(rp[v + 1] - rp[v]);
-            const bool forks = d >= static_cast<uint64_t>(a.k - 1) && d > static_cast<uint64_t>(a.threshold);
-            (*ks_off)[v + 1] = (*ks_off)[v] + (forks ? mats * d * ((d + 63) / 64) : 0);
-          }
-        }
-      }
       J.a[0] = reinterpret_cast<uint64_t>(a.row_ptr_dev);
       J.a[1] = reinterpret_cast<uint64_t>(a.col_dev);
       J.a[2] = static_cast<uint64_t>(a.n);
@@ -499,13 +590,119 @@ static int pack_job(const gtap_config &cfg, hipStream_t stream, int32_t kind, co
   }
 }
 
+// A vertex that forks row tasks (at least k-1 and more than `threshold`
+// out-neighbours; smaller ones count in place) gets its d x W bit matrix (two of
+// them for pivoting) in the job's buffer, after the vertices' n+1 offsets.
+namespace {
+
+constexpr uint32_t kKsGroup = 1024;  // vertices per workgroup of 256 threads
+
+GTAP_DEV uint64_t ks_words(const int32_t *rp, int32_t v, uint32_t k, uint32_t thr, uint32_t mats) {
+  const uint32_t d = static_cast<uint32_t>(rp[v + 1] - rp[v]);
+  return d >= k - 1 && d > thr ? static_cast<uint64_t>(mats) * d * ((d + 63) / 64) : 0ull;
+}
+
+// Matrix words per group of vertices, and whether a row is longer than
+// max_outdeg or runs backwards (counted in *bad).
+__global__ __launch_bounds__(256) void k_ks_measure(const int32_t *rp, int32_t n, int32_t max_outdeg, uint32_t k,
+                                                    uint32_t thr, uint32_t mats, uint64_t *sums, uint64_t *bad) {
+  __shared__ uint64_t part[4];
+  const int64_t v0 = static_cast<int64_t>(blockIdx.x) * kKsGroup + threadIdx.x;
+  uint64_t w = 0, wrong = 0;
+  for (uint32_t i = 0; i < kKsGroup; i += 256) {
+    const int64_t v = v0 + i;
+    if (v >= n) break;
+    const int32_t r0 = rp[v], r1 = rp[v + 1];
+    if (r1 < r0 || r1 - r0 > max_outdeg) ++wrong;
+    else if (k >= 4) w += ks_words(rp, static_cast<int32_t>(v), k, thr, mats);
+  }
+  w = readlane64(wave_inclusive_sum64(w), 63);
+  wrong = readlane64(wave_inclusive_sum64(wrong), 63);
+  if (lane_id() == 0) {
+    part[threadIdx.x / kWave] = w;
+    if (wrong) fetch_add_relaxed(bad, wrong);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+// sums[0, m) -> their exclusive prefix sums, *total the sum (one wavefront).
+__global__ __launch_bounds__(64) void k_ks_scan(uint64_t *sums, uint32_t m, uint64_t *total) {
+  uint64_t run = 0;
+  for (uint32_t i0 = 0; i0 < m; i0 += kWave) {
+    const uint32_t i = i0 + threadIdx.x;
+    const uint64_t x = i < m ? sums[i] : 0ull;
+    const uint64_t s = wave_inclusive_sum64(x);
+    if (i < m) sums[i] = run + s - x;
+    run += readlane64(s, 63);
+  }
+  if (threadIdx.x == 0) *total = run;
+}
+
+// Offsets of the vertices' matrices, n+1 of them.
+__global__ __launch_bounds__(256) void k_ks_offsets(const int32_t *rp, int32_t n, uint32_t k, uint32_t thr, uint32_t mats,
+                                                    const uint64_t *sums, uint64_t total, uint64_t *out) {
+  __shared__ uint64_t part[4];
+  const uint32_t wv = threadIdx.x / kWave;
+  uint64_t run = sums[blockIdx.x];
+  for (uint32_t i = 0; i < kKsGroup; i += 256) {
+    const int64_t v = static_cast<int64_t>(blockIdx.x) * kKsGroup + i + threadIdx.x;
+    const uint64_t x = v < n ? ks_words(rp, static_cast<int32_t>(v), k, thr, mats) : 0ull;
+    const uint64_t s = wave_inclusive_sum64(x);
+    if (lane_id() == 63) part[wv] = s;
+    __syncthreads();
+    uint64_t before = run;
+    for (uint32_t q = 0; q < 4; ++q) {
+      before += q < wv ? part[q] : 0ull;
+      run += part[q];
+    }
+    __syncthreads();
+    if (v < n) out[v] = before + s - x;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = total;
+}
+
+// Check a split k-clique job's graph against its max_outdeg (the frame buffers
+// are sized from it) and size its matrices; on the device, because copying a
+// million row bounds to the host and the offsets back took 2 ms per job.
+int ks_measure(gtap_ctx *c, const void *args, KsPlan &ks) {
+  gtap_kclique_split_args a;
+  std::memcpy(&a, args, sizeof(a));
+  if (a.n <= 0) return GTAP_OK;
+  const uint32_t groups = (static_cast<uint32_t>(a.n) + kKsGroup - 1) / kKsGroup;
+  uint64_t *sums = static_cast<uint64_t *>(c->cache.get((groups + 2) * sizeof(uint64_t)));
+  if (!sums) return GTAP_E_NOMEM;
+  uint64_t *tail = sums + groups;  // total, bad rows
+  const uint32_t k = static_cast<uint32_t>(a.k), thr = static_cast<uint32_t>(a.threshold);
+  const uint32_t mats = a.algorithm == GTAP_KCLIQUE_PIVOT ? 2 : 1;
+  bool ok = hipMemsetAsync(tail, 0, 2 * sizeof(uint64_t), c->stream) == hipSuccess;
+  if (ok) {
+    hipLaunchKernelGGL(k_ks_measure, dim3(groups), dim3(256), 0, c->stream, a.row_ptr_dev, a.n, a.max_outdeg, k, thr,
+                       mats, sums, tail + 1);
+    hipLaunchKernelGGL(k_ks_scan, dim3(1), dim3(64), 0, c->stream, sums, groups, tail);
+    ok = hipGetLastError() == hipSuccess &&
+         hipMemcpyAsync(c->pin->words, tail, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream) == hipSuccess &&
+         hipStreamSynchronize(c->stream) == hipSuccess;
+  }
+  if (!ok || c->pin->words[1] != 0 || a.k < 4) {
+    c->cache.put(sums);
+    return !ok ? GTAP_E_HIP : c->pin->words[1] != 0 ? GTAP_E_INVAL : GTAP_OK;
+  }
+  ks = KsPlan{sums, static_cast<uint64_t>(c->pin->words[0])};
+  return GTAP_OK;
+}
+
+}  // namespace
+
 extern "C" int gtap_submit(gtap_ctx *c, int32_t kind, const void *args, size_t args_bytes, uint64_t *job_id) {
   if (!c || !args) return GTAP_E_INVAL;
   if (c->serving) return GTAP_E_STATE;
   if (c->pending.size() >= c->cfg.max_jobs) return GTAP_E_FULL;
   JobSlot J;
-  std::vector<uint64_t> ks_off;
-  const int rc = pack_job(c->cfg, c->stream, kind, args, args_bytes, J, &ks_off);
+  int rc = pack_job(c->cfg, kind, args, args_bytes, J);
+  if (rc) return rc;
+  KsPlan ks{nullptr, 0};
+  if (kind == GTAP_KIND_KCLIQUE_SPLIT) rc = ks_measure(c, args, ks);
   if (rc) return rc;
   if (c->pending.empty()) {
     c->pending_first = c->next_job_id;
@@ -516,7 +713,7 @@ extern "C" int gtap_submit(gtap_ctx *c, int32_t kind, const void *args, size_t a
   gtap_fmm_args fa{};
   if (kind == GTAP_KIND_FMM) std::memcpy(&fa, args, sizeof(fa));
   c->pending_fmm.push_back(fa);
-  c->pending_ks.push_back(std::move(ks_off));
+  c->pending_ks.push_back(ks);
   if (job_id) *job_id = c->next_job_id;
   c->next_job_id++;
   return GTAP_OK;
@@ -629,7 +826,7 @@ struct FmmJobMem {
   double *Qr = nullptr, *Lr = nullptr;  // reduced ones, which M2L reads and writes
   fmm::FmmDesc *desc = nullptr;
   std::vector<std::pair<int32_t, int32_t>> levels;
-  int32_t ncells = 0;
+  int32_t ncells = 0, nleaves = 0;
   hipEvent_t ev[6] = {};
   // list-building traversals
   uint64_t *m2l = nullptr, *p2p = nullptr;
@@ -644,21 +841,22 @@ struct FmmJobMem {
   void *lsort_tmp = nullptr;
 };
 
-void fmm_free(FmmJobMem &m) {
+void fmm_free(gtap_ctx *c, FmmJobMem &m) {
   void *ptrs[] = {m.keys, m.keys_sorted, m.idx, m.perm, m.sort_tmp, m.pts, m.cell, m.parent, m.scratch,
                   m.Q, m.L, m.Qr, m.Lr, m.desc, m.m2l, m.p2p, m.front, m.seg, m.sorted, m.lsort_tmp};
   for (void *q : ptrs)
-    if (q) (void)hipFree(q);
+    if (q) c->cache.put(q);
   for (hipEvent_t &e : m.ev)
-    if (e) (void)hipEventDestroy(e);
+    if (e) c->events.put(e);
   for (hipEvent_t &e : m.lev)
-    if (e) (void)hipEventDestroy(e);
+    if (e) c->events.put(e);
   m = FmmJobMem{};
 }
 
 template <typename T>
-bool dev_alloc(T **p, size_t count) {
-  return hipMalloc(reinterpret_cast<void **>(p), sizeof(T) * (count ? count : 1)) == hipSuccess;
+bool dev_alloc(gtap_ctx *c, T **p, size_t count) {
+  *p = static_cast<T *>(c->cache.get(sizeof(T) * count));
+  return *p != nullptr;
 }
 
 unsigned nblk(int64_t n, unsigned b) { return static_cast<unsigned>(std::max<int64_t>((n + b - 1) / b, 1)); }
@@ -689,22 +887,23 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
   hipStream_t st = c->stream;
   const int32_t n = a.n;
   for (hipEvent_t &e : m.ev)
-    if (hipEventCreate(&e) != hipSuccess) return GTAP_E_HIP;
-  if (!dev_alloc(&m.keys, n) || !dev_alloc(&m.keys_sorted, n) || !dev_alloc(&m.idx, n) ||
-      !dev_alloc(&m.perm, n) || !dev_alloc(&m.pts, 5 * static_cast<size_t>(n)) ||
-      !dev_alloc(&m.scratch, 11 * (static_cast<size_t>(n) + 1) + 2))
+    if (!(e = c->events.get())) return GTAP_E_HIP;
+  if (!dev_alloc(c, &m.keys, n) || !dev_alloc(c, &m.keys_sorted, n) || !dev_alloc(c, &m.idx, n) ||
+      !dev_alloc(c, &m.perm, n) || !dev_alloc(c, &m.pts, 5 * static_cast<size_t>(n)) ||
+      !dev_alloc(c, &m.scratch, 11 * (static_cast<size_t>(n) + 1) + 3))
     return GTAP_E_NOMEM;
   int32_t *nch = m.scratch, *off = nch + (n + 1), *bnd = off + (n + 1), *flags = bnd + 9 * (static_cast<size_t>(n) + 1);
   double *px = m.pts, *py = px + n, *pz = py + n, *pq = pz + n, *phi = pq + n;
   if (hipEventRecord(m.ev[0], st) != hipSuccess) return GTAP_E_HIP;
-  if (hipMemsetAsync(flags, 0, 2 * sizeof(int32_t), st) != hipSuccess) return GTAP_E_HIP;
+  // flags: cells of the next level, points outside the cube, cells that split
+  if (hipMemsetAsync(flags, 0, 3 * sizeof(int32_t), st) != hipSuccess) return GTAP_E_HIP;
   hipLaunchKernelGGL(fmm::k_keys, dim3(nblk(n, 256)), dim3(256), 0, st, n, a.x_dev, a.y_dev, a.z_dev, m.keys,
                      m.idx, flags + 1);
   size_t tmp_bytes = 0;
   if (rocprim::radix_sort_pairs(nullptr, tmp_bytes, m.keys, m.keys_sorted, m.idx, m.perm,
                                 static_cast<size_t>(n), 0, 63, st) != hipSuccess)
     return GTAP_E_HIP;
-  if (hipMalloc(&m.sort_tmp, tmp_bytes ? tmp_bytes : 1) != hipSuccess) return GTAP_E_NOMEM;
+  if (!(m.sort_tmp = c->cache.get(tmp_bytes))) return GTAP_E_NOMEM;
   if (rocprim::radix_sort_pairs(m.sort_tmp, tmp_bytes, m.keys, m.keys_sorted, m.idx, m.perm,
                                 static_cast<size_t>(n), 0, 63, st) != hipSuccess)
     return GTAP_E_HIP;
@@ -712,8 +911,8 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
                      a.q_dev, px, py, pz, pq, phi);
   // octree, one level at a time (the host learns each level's size)
   m.cell_cap = 2 * static_cast<int64_t>(n) + 64;
-  if (!dev_alloc(&m.cell, static_cast<size_t>(m.cell_cap) * fmm::kCellInts) ||
-      !dev_alloc(&m.parent, static_cast<size_t>(m.cell_cap)))
+  if (!dev_alloc(c, &m.cell, static_cast<size_t>(m.cell_cap) * fmm::kCellInts) ||
+      !dev_alloc(c, &m.parent, static_cast<size_t>(m.cell_cap)))
     return GTAP_E_NOMEM;
   hipLaunchKernelGGL(fmm::k_root, dim3(1), dim3(64), 0, st, m.cell, m.parent, n);
   int32_t lo = 0, hi = 1;
@@ -722,10 +921,10 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
   for (;;) {
     const int32_t w = hi - lo;
     hipLaunchKernelGGL(fmm::k_level_count, dim3(nblk(w, 256)), dim3(256), 0, st, m.cell, lo, hi, m.keys_sorted,
-                       a.leaf_max, nch, bnd);
+                       a.leaf_max, nch, bnd, flags + 2);
     hipLaunchKernelGGL(fmm::k_scan, dim3(1), dim3(1024), 0, st, nch, off, w, flags);
-    int32_t hf[2] = {0, 0};
-    if (hipMemcpyAsync(hf, flags, sizeof(hf), hipMemcpyDeviceToHost, st) != hipSuccess ||
+    int32_t *hf = reinterpret_cast<int32_t *>(c->pin->words);
+    if (hipMemcpyAsync(hf, flags, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
       return GTAP_E_HIP;
     if (hf[1] != 0) return GTAP_E_INVAL;  // a point outside the root cube
@@ -734,15 +933,17 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
     if (hi + static_cast<int64_t>(total) > m.cell_cap) {
       const int64_t cap2 = std::max<int64_t>(2 * m.cell_cap, hi + static_cast<int64_t>(total) + 64);
       int32_t *c2 = nullptr, *p2 = nullptr;
-      if (!dev_alloc(&c2, static_cast<size_t>(cap2) * fmm::kCellInts) || !dev_alloc(&p2, static_cast<size_t>(cap2)))
+      if (!dev_alloc(c, &c2, static_cast<size_t>(cap2) * fmm::kCellInts) || !dev_alloc(c, &p2, static_cast<size_t>(cap2))) {
+        if (c2) c->cache.put(c2);
         return GTAP_E_NOMEM;
+      }
       if (hipMemcpyAsync(c2, m.cell, sizeof(int32_t) * fmm::kCellInts * hi, hipMemcpyDeviceToDevice, st) !=
               hipSuccess ||
           hipMemcpyAsync(p2, m.parent, sizeof(int32_t) * hi, hipMemcpyDeviceToDevice, st) != hipSuccess ||
           hipStreamSynchronize(st) != hipSuccess)
         return GTAP_E_HIP;
-      (void)hipFree(m.cell);
-      (void)hipFree(m.parent);
+      c->cache.put(m.cell);
+      c->cache.put(m.parent);
       m.cell = c2;
       m.parent = p2;
       m.cell_cap = cap2;
@@ -754,11 +955,12 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
     m.levels.emplace_back(lo, hi);
   }
   m.ncells = hi;
+  m.nleaves = hi - reinterpret_cast<const int32_t *>(c->pin->words)[2];
   if (hipEventRecord(m.ev[1], st) != hipSuccess) return GTAP_E_HIP;
-  if (!dev_alloc(&m.Q, static_cast<size_t>(m.ncells) * fmm::kNc) ||
-      !dev_alloc(&m.L, static_cast<size_t>(m.ncells) * fmm::kNc) ||
-      !dev_alloc(&m.Qr, static_cast<size_t>(m.ncells) * fmm::kQrStride) ||
-      !dev_alloc(&m.Lr, static_cast<size_t>(m.ncells) * fmm::kNr))
+  if (!dev_alloc(c, &m.Q, static_cast<size_t>(m.ncells) * fmm::kNc) ||
+      !dev_alloc(c, &m.L, static_cast<size_t>(m.ncells) * fmm::kNc) ||
+      !dev_alloc(c, &m.Qr, static_cast<size_t>(m.ncells) * fmm::kQrStride) ||
+      !dev_alloc(c, &m.Lr, static_cast<size_t>(m.ncells) * fmm::kNr))
     return GTAP_E_NOMEM;
   if (a.traversal == GTAP_FMM_TASKS &&  // the list evaluation writes every cell's
       hipMemsetAsync(m.Lr, 0, sizeof(double) * fmm::kNr * m.ncells, st) != hipSuccess)
@@ -789,15 +991,16 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
       m.m2l_cap += static_cast<uint64_t>(c->nwaves) * fmm::kListChunk;
       m.p2p_cap += static_cast<uint64_t>(c->nwaves) * fmm::kListChunk;
     }
-    if (!dev_alloc(&m.m2l, m.m2l_cap) || !dev_alloc(&m.p2p, m.p2p_cap)) return GTAP_E_NOMEM;
+    if (!dev_alloc(c, &m.m2l, m.m2l_cap) || !dev_alloc(c, &m.p2p, m.p2p_cap)) return GTAP_E_NOMEM;
     d.m2l_list = m.m2l;
     d.p2p_list = m.p2p;
     d.m2l_cap = m.m2l_cap;
     d.p2p_cap = m.p2p_cap;
   }
   m.hdesc = d;
-  if (!dev_alloc(&m.desc, 1)) return GTAP_E_NOMEM;
-  if (hipMemcpyAsync(m.desc, &d, sizeof(d), hipMemcpyHostToDevice, st) != hipSuccess ||
+  if (!dev_alloc(c, &m.desc, 1)) return GTAP_E_NOMEM;
+  c->pin->desc = d;  // (no copy from it is in flight: every level read its sizes back)
+  if (hipMemcpyAsync(m.desc, &c->pin->desc, sizeof(d), hipMemcpyHostToDevice, st) != hipSuccess ||
       hipStreamSynchronize(st) != hipSuccess)
     return GTAP_E_HIP;
   return hipGetLastError() == hipSuccess ? GTAP_OK : GTAP_E_HIP;
@@ -807,16 +1010,16 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
 // their counters and the descriptor's statistics.
 int fmm_grow_lists(gtap_ctx *c, FmmJobMem &m, uint64_t need_m2l, uint64_t need_p2p) {
   if (need_m2l > m.m2l_cap) {
-    (void)hipFree(m.m2l);
+    c->cache.put(m.m2l);
     m.m2l = nullptr;
     m.m2l_cap = need_m2l + need_m2l / 4 + 1024;
-    if (!dev_alloc(&m.m2l, m.m2l_cap)) return GTAP_E_NOMEM;
+    if (!dev_alloc(c, &m.m2l, m.m2l_cap)) return GTAP_E_NOMEM;
   }
   if (need_p2p > m.p2p_cap) {
-    (void)hipFree(m.p2p);
+    c->cache.put(m.p2p);
     m.p2p = nullptr;
     m.p2p_cap = need_p2p + need_p2p / 4 + 1024;
-    if (!dev_alloc(&m.p2p, m.p2p_cap)) return GTAP_E_NOMEM;
+    if (!dev_alloc(c, &m.p2p, m.p2p_cap)) return GTAP_E_NOMEM;
   }
   fmm::FmmDesc &d = m.hdesc;
   d.m2l_list = m.m2l;
@@ -833,13 +1036,13 @@ int fmm_grow_lists(gtap_ctx *c, FmmJobMem &m, uint64_t need_m2l, uint64_t need_p
 
 // The list counters after a traversal (they count past the capacities).
 int fmm_list_counts(gtap_ctx *c, const FmmJobMem &m, uint64_t &n_m2l, uint64_t &n_p2p) {
-  uint64_t v[2] = {0, 0};
+  int64_t *v = c->pin->words;
   static_assert(offsetof(fmm::FmmDesc, p2p_n) == offsetof(fmm::FmmDesc, m2l_n) + sizeof(uint64_t), "counters");
-  if (hipMemcpyAsync(v, &m.desc->m2l_n, sizeof(v), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+  if (hipMemcpyAsync(v, &m.desc->m2l_n, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess)
     return GTAP_E_HIP;
-  n_m2l = v[0];
-  n_p2p = v[1];
+  n_m2l = static_cast<uint64_t>(v[0]);
+  n_p2p = static_cast<uint64_t>(v[1]);
   return GTAP_OK;
 }
 
@@ -849,11 +1052,11 @@ int fmm_list_counts(gtap_ctx *c, const FmmJobMem &m, uint64_t &n_m2l, uint64_t &
 int fmm_worklist(gtap_ctx *c, FmmJobMem &m) {
   hipStream_t st = c->stream;
   for (hipEvent_t &e : m.lev)
-    if (!e && hipEventCreate(&e) != hipSuccess) return GTAP_E_HIP;
+    if (!e && !(e = c->events.get())) return GTAP_E_HIP;
   if (!m.front) {
     // a frontier holds the pairs of one level (grown and re-run if not)
     m.front_cap = std::max<uint64_t>(1u << 20, (m.m2l_cap + m.p2p_cap) / 2);
-    if (!dev_alloc(&m.front, 2 * m.front_cap + 1)) return GTAP_E_NOMEM;
+    if (!dev_alloc(c, &m.front, 2 * m.front_cap + 1)) return GTAP_E_NOMEM;
   }
   for (int attempt = 0; attempt < 4; ++attempt) {
     if (hipEventRecord(m.lev[0], st) != hipSuccess) return GTAP_E_HIP;
@@ -868,9 +1071,10 @@ int fmm_worklist(gtap_ctx *c, FmmJobMem &m) {
       hipLaunchKernelGGL(fmm::k_dtt_frontier,
                          dim3(static_cast<unsigned>((nin + fmm::kFrontierThreads - 1) / fmm::kFrontierThreads)),
                          dim3(fmm::kFrontierThreads), 0, st, m.desc, fin, nin, fout, cnt, m.front_cap);
-      if (hipMemcpyAsync(&nout, cnt, sizeof(nout), hipMemcpyDeviceToHost, st) != hipSuccess ||
+      if (hipMemcpyAsync(c->pin->words, cnt, sizeof(nout), hipMemcpyDeviceToHost, st) != hipSuccess ||
           hipStreamSynchronize(st) != hipSuccess)
         return GTAP_E_HIP;
+      nout = static_cast<uint64_t>(c->pin->words[0]);
       ++rounds;
       if (nout > m.front_cap) {
         over = true;
@@ -889,10 +1093,10 @@ int fmm_worklist(gtap_ctx *c, FmmJobMem &m) {
     }
     ++m.retries;
     if (over) {
-      (void)hipFree(m.front);
+      c->cache.put(m.front);
       m.front = nullptr;
       m.front_cap = 2 * nout;
-      if (!dev_alloc(&m.front, 2 * m.front_cap + 1)) return GTAP_E_NOMEM;
+      if (!dev_alloc(c, &m.front, 2 * m.front_cap + 1)) return GTAP_E_NOMEM;
     }
     rc = fmm_grow_lists(c, m, over ? 0 : n_m2l, over ? 0 : n_p2p);
     if (rc) return rc;
@@ -906,7 +1110,7 @@ int fmm_worklist(gtap_ctx *c, FmmJobMem &m) {
 int fmm_eval_lists(gtap_ctx *c, FmmJobMem &m, uint64_t n_m2l, uint64_t n_p2p, gtap_fmm_result &r) {
   hipStream_t st = c->stream;
   for (hipEvent_t &e : m.lev)
-    if (!e && hipEventCreate(&e) != hipSuccess) return GTAP_E_HIP;
+    if (!e && !(e = c->events.get())) return GTAP_E_HIP;
   const uint64_t nmax = std::max<uint64_t>(std::max(n_m2l, n_p2p), 1);
   unsigned end_bit = 32;
   while (end_bit < 64 && (static_cast<uint64_t>(m.ncells) >> (end_bit - 32)) != 0) ++end_bit;
@@ -916,8 +1120,8 @@ int fmm_eval_lists(gtap_ctx *c, FmmJobMem &m, uint64_t n_m2l, uint64_t n_p2p, gt
     return GTAP_E_HIP;
   // segments of targets 0..ncells (ncells: the gaps of chunked appends)
   const size_t nseg = static_cast<size_t>(m.ncells) + 1;
-  if (!dev_alloc(&m.sorted, nmax) || !dev_alloc(&m.seg, 2 * nseg) ||
-      hipMalloc(&m.lsort_tmp, tmp_bytes ? tmp_bytes : 1) != hipSuccess)
+  if (!dev_alloc(c, &m.sorted, nmax) || !dev_alloc(c, &m.seg, 2 * nseg) ||
+      !(m.lsort_tmp = c->cache.get(tmp_bytes)))
     return GTAP_E_NOMEM;
   uint64_t *lo = m.seg, *hi = m.seg + nseg;
   fmm::FmmDesc *D = m.desc;
@@ -971,16 +1175,13 @@ int fmm_finish(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m, float traversa
   hipLaunchKernelGGL(fmm::k_l2p, dim3(m.ncells), dim3(64), 0, st, m.cell, 0, m.ncells, m.L, px, py, pz, phi);
   hipLaunchKernelGGL(fmm::k_scatter, dim3(nblk(n, 256)), dim3(256), 0, st, n, m.perm, phi, a.phi_dev);
   if (hipEventRecord(m.ev[4], st) != hipSuccess) return GTAP_E_HIP;
-  fmm::FmmDesc d{};
-  std::vector<int32_t> cells(static_cast<size_t>(m.ncells) * fmm::kCellInts);
-  if (hipMemcpyAsync(&d, m.desc, sizeof(d), hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipMemcpyAsync(cells.data(), m.cell, sizeof(int32_t) * cells.size(), hipMemcpyDeviceToHost, st) !=
-          hipSuccess ||
+  const fmm::FmmDesc &d = c->pin->desc;
+  if (hipMemcpyAsync(&c->pin->desc, m.desc, sizeof(d), hipMemcpyDeviceToHost, st) != hipSuccess ||
       hipStreamSynchronize(st) != hipSuccess)
     return GTAP_E_HIP;
   r = gtap_fmm_result{};
   r.n_cells = m.ncells;
-  for (int32_t i = 0; i < m.ncells; ++i) r.n_leaves += cells[static_cast<size_t>(i) * fmm::kCellInts + 7] == 0;
+  r.n_leaves = m.nleaves;
   r.max_level = static_cast<int64_t>(m.levels.size()) - 1;
   r.m2l_pairs = static_cast<int64_t>(d.m2l_pairs);
   r.p2p_pairs = static_cast<int64_t>(d.p2p_pairs);
@@ -1026,25 +1227,31 @@ int gtap_run(gtap_ctx *c) {
   }
   std::vector<void *> ks_mem;
   auto drop_pending = [&]() {
-    for (FmmJobMem &m : fm) fmm_free(m);
-    for (void *q : ks_mem) (void)hipFree(q);
+    for (FmmJobMem &m : fm) fmm_free(c, m);
+    for (void *q : ks_mem) c->cache.put(q);
+    for (const KsPlan &ks : c->pending_ks)
+      if (ks.sums) c->cache.put(ks.sums);
+    c->cache.trim(kCacheBytes);
     c->pending.clear();
     c->pending_fmm.clear();
     c->pending_ks.clear();
   };
   // split k-clique jobs: offsets and bit matrices in one device buffer
   for (size_t j = 0; j < nj; ++j) {
-    const std::vector<uint64_t> &off = c->pending_ks[j];
-    if (c->pending[j].kind != GTAP_KIND_KCLIQUE_SPLIT || off.empty()) continue;
-    void *q = nullptr;
-    const size_t words = off.size() + off.back();
-    if (hipMalloc(&q, words * sizeof(uint64_t)) != hipSuccess) {
+    const KsPlan &ks = c->pending_ks[j];
+    if (!ks.sums) continue;
+    const JobSlot &J = c->pending[j];
+    const int32_t n = static_cast<int32_t>(J.a[2]);
+    uint64_t *q = static_cast<uint64_t *>(c->cache.get((static_cast<size_t>(n) + 1 + ks.words) * sizeof(uint64_t)));
+    if (!q) {
       drop_pending();
       return GTAP_E_NOMEM;
     }
     ks_mem.push_back(q);
-    if (hipMemcpyAsync(q, off.data(), off.size() * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream) !=
-        hipSuccess) {
+    hipLaunchKernelGGL(k_ks_offsets, dim3((static_cast<uint32_t>(n) + kKsGroup - 1) / kKsGroup), dim3(256), 0, c->stream,
+                       reinterpret_cast<const int32_t *>(J.a[0]), n, static_cast<uint32_t>(J.a[3]),
+                       static_cast<uint32_t>(J.a[6] & 0xFFu), ((J.a[6] >> 8) & 1u) ? 2u : 1u, ks.sums, ks.words, q);
+    if (hipGetLastError() != hipSuccess) {
       drop_pending();
       return GTAP_E_HIP;
     }
@@ -1072,12 +1279,14 @@ int gtap_run(gtap_ctx *c) {
   }
   // one launch; a list-building traversal whose lists overflowed is re-run
   // with lists that fit (every job of the batch runs again)
-  Control ctl;
+  const bool pinned = nj <= kPinnedJobs;
+  const Control &ctl = c->pin->ctl;
   float ms = 0.f;
   int rc = GTAP_OK;
   for (int attempt = 0;; ++attempt) {
-    if (hipMemcpyAsync(p.jobs, c->pending.data(), nj * sizeof(JobSlot), hipMemcpyHostToDevice, c->stream) !=
-        hipSuccess) {
+    if (pinned) std::memcpy(c->pin->jobs, c->pending.data(), nj * sizeof(JobSlot));
+    if (hipMemcpyAsync(p.jobs, pinned ? c->pin->jobs : c->pending.data(), nj * sizeof(JobSlot), hipMemcpyHostToDevice,
+                       c->stream) != hipSuccess) {
       drop_pending();
       return GTAP_E_HIP;
     }
@@ -1092,13 +1301,14 @@ int gtap_run(gtap_ctx *c) {
       return rc;
     }
     c->done_jobs.resize(nj);
-    if (hipMemcpyAsync(c->done_jobs.data(), p.jobs, nj * sizeof(JobSlot), hipMemcpyDeviceToHost, c->stream) !=
-            hipSuccess ||
-        hipMemcpyAsync(&ctl, p.ctl, sizeof(Control), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+    if (hipMemcpyAsync(pinned ? c->pin->jobs : c->done_jobs.data(), p.jobs, nj * sizeof(JobSlot), hipMemcpyDeviceToHost,
+                       c->stream) != hipSuccess ||
+        hipMemcpyAsync(&c->pin->ctl, p.ctl, sizeof(Control), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess) {
       drop_pending();
       return GTAP_E_HIP;
     }
+    if (pinned) std::memcpy(c->done_jobs.data(), c->pin->jobs, nj * sizeof(JobSlot));
     (void)hipEventElapsedTime(&ms, c->ev0, c->ev1);
     bool again = false;
     if (ctl.error == 0 && any_fmm && !block) {
@@ -1215,7 +1425,7 @@ int gtap_serve_submit(gtap_ctx *c, int32_t kind, const void *args, size_t args_b
   // no split k-clique search
   if (kind == GTAP_KIND_FMM || kind == GTAP_KIND_CILKSORT || kind == GTAP_KIND_KCLIQUE_SPLIT) return GTAP_E_INVAL;
   JobSlot J;
-  const int rc = pack_job(c->cfg, c->stream, kind, args, args_bytes, J);
+  const int rc = pack_job(c->cfg, kind, args, args_bytes, J);
   if (rc) return rc;
   const uint64_t t = c->next_ticket;
   const uint64_t R = c->params.ring_cap;
@@ -1502,6 +1712,9 @@ int gtap_finalize(gtap_ctx *c) {
   else (void)hipDeviceSynchronize();
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
+  c->cache.clear();
+  c->events.clear();
+  if (c->pin) (void)hipHostFree(c->pin);
   if (c->owns_ws && c->ws) (void)hipFree(c->ws);
   if (c->ring) (void)hipHostFree(c->ring);
   if (c->ring_seq) (void)hipHostFree(c->ring_seq);
@@ -1728,7 +1941,7 @@ extern "C" int gtap_run_static(const gtap_config *cfg_in, const gtap_trace_job *
   for (size_t i0 = 0; i0 < n; i0 += kStaticChunk) {
     const size_t m = std::min(kStaticChunk, n - i0);
     for (size_t i = 0; i < m; ++i) {
-      rc = pack_job(cfg, c.stream, jobs[i0 + i].kind, jobs[i0 + i].args, jobs[i0 + i].args_bytes, buf[i]);
+      rc = pack_job(cfg, jobs[i0 + i].kind, jobs[i0 + i].args, jobs[i0 + i].args_bytes, buf[i]);
       if (rc) return rc;
     }
     if (hipMemcpyAsync(p.jobs + i0, buf, m * sizeof(JobSlot), hipMemcpyHostToDevice, c.stream) != hipSuccess ||
