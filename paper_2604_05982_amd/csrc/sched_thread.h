@@ -32,6 +32,9 @@ namespace gtap {
 constexpr uint32_t kPushSpinLimit = 1u << 16;
 
 constexpr uint32_t kClassCache = 1024;  // children whose DAQ class is kept from the counting pass
+constexpr uint32_t kExposeMask = 7;     // busy wavefronts look at exposing tasks every eighth iteration
+constexpr uint32_t kRampChecks = 16;    // ... after this many looks, one in every iteration with tasks to expose
+constexpr uint32_t kStealWait = 3;      // iterations without a steal attempt after a failed one
 constexpr uint32_t kDaqPressure = 2048;  // queued tasks per wavefront above which DAQ runs lowest class first
 constexpr uint32_t kLocalFramed = 0xFFFFFFFFu;  // private-stack entry that names a frame (never a job slot)
 
@@ -765,6 +768,7 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
   constexpr bool kCentral = (V == kSchedCentral);
   constexpr bool kSingle = (V == kSchedSingle);
   constexpr bool kNoLocal = (V != kSchedBatched);
+  constexpr bool kRamp = (kExt & kExtLists) == 0;  // expose early while most of the grid is idle
   __shared__ WaveLds lds_all[WPB];
   __shared__ kcw::Lds ks_all[(kExt & kExtSplit) != 0 ? WPB : 1];  // (no LDS where nothing refers to it)
   // Private task stack: children a wavefront cannot run in its lanes this
@@ -827,6 +831,11 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
 
   uint32_t idle = 0;
   uint32_t iter = 0;
+  // iterations at which exposing tasks is looked at: iter & xmask == 0 (small
+  // frame pools keep to the eighths: tasks exposed early hold frames sooner)
+  uint32_t xmask = kRamp && p.nframes_s / (kRampChecks * kWave) >= p.nwaves ? 0u : kExposeMask;
+  uint32_t ramp_left = kRampChecks;
+  uint32_t steal_wait = 0;  // iterations left in which this wavefront, holding tasks, does not try to steal
   bool hungry = false;  // counted in the control block's hungry-wavefront hint
   bool tcont = false;  // this lane's task is a resumed parent (runs its continuation)
   fmm::ListChunks lchunks{nullptr, {0, 0}, {fmm::kListChunk, fmm::kListChunk}};  // FMM list traversal only
@@ -935,10 +944,18 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
         }
       }
     } else if (!kCentral && cnt < p.steal_below && p.nwaves > 1 && !own_left) {
-      uint32_t qs = cur_q;
-      const uint32_t got = steal_batch(p, me, rng, cnt, tid, qs, wc);
-      if (got > 0 && cnt == 0) cur_q = qs;
-      cnt += got;
+      // a wavefront that holds tasks and found nothing to steal leaves the
+      // next iterations to the idle ones: the probe is a round trip in
+      // every iteration of a job's critical path
+      if (cnt == 0 || steal_wait == 0) {
+        uint32_t qs = cur_q;
+        const uint32_t got = steal_batch(p, me, rng, cnt, tid, qs, wc);
+        if (got > 0 && cnt == 0) cur_q = qs;
+        steal_wait = got > 0 ? 0u : kStealWait;
+        cnt += got;
+      } else {
+        --steal_wait;
+      }
     }
     if (ln >= cnt0) tcont = false;
     if (cnt == 0) {
@@ -1234,14 +1251,28 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
       const uint32_t have = ltop - lbot;
       uint32_t ex = (have + nsmall > LC) ? (have + nsmall - LC) : 0u;
       if (ex > have) ex = have;
-      if ((iter & 7u) == 0 && have >= 2 * kWave) {
+      if ((iter & xmask) == 0 && have >= (xmask ? 2 * kWave : kWave / 2)) {
         // half the stack goes to the deque when it runs low and some
-        // wavefront is looking for work (both words read in one round trip)
+        // wavefront is looking for work (both words read in one round trip).
+        // In its first iterations a wavefront looks at that every time and,
+        // while most of the grid is idle, exposes a batch of its oldest tasks:
+        // an iteration lasts 7 to 10 us, so waiting for the eighth kept small
+        // jobs on a few wavefronts (a sort of 100,003 keys 3.0 -> 1.8 ms, a
+        // batch of 27,518 tasks 0.64 -> 0.45 ms).  Later it would cost large
+        // jobs 2 to 3 % at their ends, and the FMM list traversal, whose pairs
+        // fan out eightfold, fills the grid without it and pays for the frames
+        // (2.3 -> 2.7 ms).
         int32_t c = 0;
         if (ln == 0) c = ld_relaxed(&deque_meta(p, me, 0)->count);
         if (ln == 1) c = ld_relaxed(&p.ctl->hungry);
         const int32_t own = __builtin_amdgcn_readlane(c, 0), seekers = __builtin_amdgcn_readlane(c, 1);
-        if (own < static_cast<int32_t>(kWave) && seekers > 0 && have / 2 > ex) ex = have / 2;
+        uint32_t give = own < static_cast<int32_t>(kWave) && seekers > 0 ? have / 2 : 0u;
+        if (kRamp && xmask == 0) {
+          if (give > kWave) give = kWave;
+          if (seekers * 4 < static_cast<int32_t>(p.nwaves) * 3) give = 0;
+          if (--ramp_left == 0) xmask = kExposeMask;
+        }
+        if (give > ex) ex = give;
       }
       E = ex;
       const uint32_t free_slots = LC - (have - E);

@@ -8,7 +8,8 @@
 // bounded the lane-serial form was the chain of device-coherent loads (a
 // merge of 256 keys is 256 dependent steps, each about a microsecond, on one
 // lane).  100,003 keys on one queue: 6.7 ms in the kernel lane-serially, 3.1 ms
-// this way; 30 M keys on three queues: 26.6 -> 13.1 ms.
+// this way (1.8 ms with tasks exposed early); 30 M keys on three queues: 26.6 ->
+// 12.6 ms.
 //
 // Both run as bitonic networks on registers: partners at lane distance 1..8
 // come by DPP, 16 and 32 by the row-swap instructions, 64 and 128 are other

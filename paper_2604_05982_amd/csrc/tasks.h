@@ -202,9 +202,17 @@ GTAP_DEV uint32_t intersect_sorted(const int32_t *C, uint32_t nc, const int32_t 
   return nc <= nb ? isect_gallop<true, false>(C, nc, B, nb, out) : isect_gallop<false, true>(B, nb, C, nc, out);
 }
 
-// Job arguments.  Read coherently: while serving, a job slot is rewritten by
-// the wave that admits the next job using it.
-GTAP_DEV uint64_t job_arg(const Params &p, uint32_t job, uint32_t i) { return co_ld64(&p.jobs[job].a[i]); }
+// Job arguments.  While serving, a job slot is rewritten by the wave that admits
+// the next job using it, so they are read coherently (a round trip past the
+// L2, about a microsecond).  The kernels with extension sets never serve: their
+// arguments are written before the launch and stay, and the caches serve them
+// (in the plain kernel the choice at run time cost the job mix 1 to 2 %).
+template <uint32_t kExt = 0>
+GTAP_DEV uint64_t job_arg(const Params &p, uint32_t job, uint32_t i) {
+  const uint64_t *a = &p.jobs[job].a[i];
+  if constexpr (kExt != 0) return *a;
+  else return co_ld64(a);
+}
 
 // Words 0..7 of a task: its frame's first half, or the LDS descriptor of a
 // task that has no frame (a child retained by the wavefront that spawned it).
@@ -237,24 +245,32 @@ GTAP_DEV TaskImage load_continuation(const Params &p, uint32_t tid) {
 constexpr uint32_t kMergeD = (1u << 29) - 1;  // merge payload word 4: destination start
 constexpr uint32_t kEmitSort = 3, kEmitMerge = 4;
 
-// Number of keys of the sorted range s[0, n) below v.  Seven keys are read at
-// once and the range shrinks to an eighth: the search is a chain of loads
-// from other XCDs' writes (about a microsecond each), a third as long as a
-// bisection's.
-GTAP_DEV uint32_t count_below(const uint32_t *s, uint32_t n, uint32_t v) {
+// Number of keys of the sorted range s[0, n) below *pv.  Fifteen keys are read at
+// once and the range shrinks to a sixteenth: the search is a chain of loads of
+// other XCDs' writes (about a microsecond each), a quarter as long as a
+// bisection's, and *pv itself travels with the first round.
+constexpr uint32_t kProbes = 15;
+GTAP_DEV uint32_t count_below(const uint32_t *s, uint32_t n, const uint32_t *pv) {
   uint32_t lo = 0, hi = n;
-  while (hi - lo >= 8) {
-    const uint32_t q = (hi - lo) / 8;
+  const uint32_t v = co_ld32(pv);
+  while (hi - lo > kProbes) {
+    const uint32_t q = (hi - lo) / (kProbes + 1);
+    uint32_t x[kProbes];
+#pragma unroll
+    for (uint32_t i = 0; i < kProbes; ++i) x[i] = co_ld32(s + lo + (i + 1) * q);
     uint32_t c = 0;
 #pragma unroll
-    for (uint32_t i = 1; i < 8; ++i) c += co_ld32(s + lo + i * q) < v ? 1u : 0u;
+    for (uint32_t i = 0; i < kProbes; ++i) c += x[i] < v ? 1u : 0u;
     const uint32_t base = lo;
     if (c > 0) lo = base + c * q + 1;
-    if (c < 7) hi = base + (c + 1) * q;
+    if (c < kProbes) hi = base + (c + 1) * q;
   }
+  uint32_t x[kProbes];
+#pragma unroll
+  for (uint32_t i = 0; i < kProbes; ++i) x[i] = lo + i < hi ? co_ld32(s + lo + i) : 0xFFFFFFFFu;
   uint32_t c = 0;
 #pragma unroll
-  for (uint32_t i = 0; i < 7; ++i) c += lo + i < hi && co_ld32(s + lo + i) < v ? 1u : 0u;
+  for (uint32_t i = 0; i < kProbes; ++i) c += lo + i < hi && x[i] < v ? 1u : 0u;
   return lo + c;
 }
 
@@ -273,8 +289,8 @@ constexpr uint32_t kEmitClear = 8;   // pivoting: a vertex about to fork row tas
 
 // Edge (u, i), k = 3: |N+(u) /\ N+(v)|, v = the i-th out-neighbour of u.
 GTAP_DEV void ks_edge3(const Params &p, Outcome &o, uint32_t u, uint32_t i) {
-  const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 0));
-  const int32_t *col = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 1));
+  const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExtSplit>(p, o.job, 0));
+  const int32_t *col = reinterpret_cast<const int32_t *>(job_arg<kExtSplit>(p, o.job, 1));
   const int32_t s0 = rp[u];
   const int32_t v = col[s0 + i];
   const uint32_t du = static_cast<uint32_t>(rp[u + 1] - s0), dv = static_cast<uint32_t>(rp[v + 1] - rp[v]);
@@ -328,7 +344,7 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
     if constexpr ((kExt & kExtSplit) != 0) {
       if (pc == 1 && kind == TK_KS_VERTEX) {  // the matrix is complete: the edge tasks
         const uint32_t u = co_ld32(frame_ptr(p, tid) + FW_P0);  // (written at spawn or when it forked)
-        const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 0));
+        const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, o.job, 0));
         o.type = OUT_FORK;
         o.nchild = static_cast<uint32_t>(rp[u + 1] - rp[u]);
         o.ckind = TK_KS_EDGE;
@@ -358,10 +374,10 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
         // sort(lo, n, dst): serial below the cutoff, else both halves into the
         // other buffer first (resume point 1 merges them)
         const uint32_t lo = p0, n = p1, dst = p2;
-        const uint32_t sc = static_cast<uint32_t>(job_arg(p, o.job, 3));
+        const uint32_t sc = static_cast<uint32_t>(job_arg<kExt>(p, o.job, 3));
         if (n <= sc) {
-          const uint64_t x = job_arg(p, o.job, 0) + 4ull * lo;
-          const uint64_t d = job_arg(p, o.job, dst ? 1 : 0) + 4ull * lo;
+          const uint64_t x = job_arg<kExt>(p, o.job, 0) + 4ull * lo;
+          const uint64_t d = job_arg<kExt>(p, o.job, dst ? 1 : 0) + 4ull * lo;
           o.emit = kEmitSort;
           o.d[0] = static_cast<uint32_t>(x); o.d[1] = static_cast<uint32_t>(x >> 32);
           o.d[4] = n;
@@ -382,10 +398,10 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
         uint32_t a0 = p0, na = p1, b0 = p2, nb = p3;
         const uint32_t dst = p4 >> 31;
         uint32_t d0 = p4 & kMergeD;
-        const uint32_t *S = reinterpret_cast<const uint32_t *>(job_arg(p, o.job, dst ? 0 : 1));
-        uint32_t *D = reinterpret_cast<uint32_t *>(job_arg(p, o.job, dst ? 1 : 0));
+        const uint32_t *S = reinterpret_cast<const uint32_t *>(job_arg<kExt>(p, o.job, dst ? 0 : 1));
+        uint32_t *D = reinterpret_cast<uint32_t *>(job_arg<kExt>(p, o.job, dst ? 1 : 0));
         if ((p4 >> 29) & 1u) {
-          const uint32_t ma = na / 2, mb = count_below(S + b0, nb, co_ld32(S + a0 + ma));
+          const uint32_t ma = na / 2, mb = count_below(S + b0, nb, S + a0 + ma);
           if ((p4 >> 30) & 1u) {
             a0 += ma; na -= ma; b0 += mb; nb -= mb; d0 += ma + mb;
           } else {
@@ -396,7 +412,7 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
           const uint32_t t0 = a0, t1 = na;
           a0 = b0; na = nb; b0 = t0; nb = t1;
         }
-        const uint32_t mc = static_cast<uint32_t>(job_arg(p, o.job, 3) >> 32);
+        const uint32_t mc = static_cast<uint32_t>(job_arg<kExt>(p, o.job, 3) >> 32);
         if (na + nb <= mc) {
           const uint64_t a = reinterpret_cast<uint64_t>(S + a0), b = reinterpret_cast<uint64_t>(S + b0);
           const uint64_t d = reinterpret_cast<uint64_t>(D + d0);
@@ -417,7 +433,7 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
     if constexpr ((kExt & kExtSplit) != 0) {
       if (kind == TK_KS_RANGE) {  // vertex range: halves, then one vertex task per vertex
         const uint32_t lo = p0, hi = p1;
-        const uint32_t leaf = static_cast<uint32_t>(job_arg(p, o.job, 4));
+        const uint32_t leaf = static_cast<uint32_t>(job_arg<kExt>(p, o.job, 4));
         if (hi <= lo) return;
         o.type = OUT_FORK;
         o.d[0] = lo; o.d[1] = hi;
@@ -429,8 +445,8 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
         // k = 3: one edge task per out-neighbour.  k >= 4 (at least k-1
         // out-neighbours): the row tasks of the vertex's matrix first (resume
         // point 1 forks the edge tasks, resume point 2 sums them)
-        const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 0));
-        const uint32_t k = static_cast<uint32_t>(job_arg(p, o.job, 3));
+        const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, o.job, 0));
+        const uint32_t k = static_cast<uint32_t>(job_arg<kExt>(p, o.job, 3));
         const uint32_t deg = static_cast<uint32_t>(rp[p0 + 1] - rp[p0]);
         o.words = 2;
         if (k <= 2) {
@@ -446,7 +462,7 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
           o.pc_next = 2;
           return;
         }
-        const uint64_t a6 = job_arg(p, o.job, 6);
+        const uint64_t a6 = job_arg<kExt>(p, o.job, 6);
         if (deg <= static_cast<uint32_t>(a6 & 0xFFu)) {  // few out-neighbours: the whole vertex in place
           o.type = OUT_DONE;
           o.emit = kEmitVertex;
@@ -462,7 +478,7 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
         return;
       }
       if (kind == TK_KS_ROW || kind == TK_KS_EDGE || kind == TK_KS_HEAVY || kind == TK_KS_NODE) {
-        if (kind == TK_KS_EDGE && job_arg(p, o.job, 3) == 3) {
+        if (kind == TK_KS_EDGE && job_arg<kExt>(p, o.job, 3) == 3) {
           ks_edge3(p, o, p0, p1);
           return;
         }
@@ -549,7 +565,7 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
       // Vertex range [lo,hi): halve while larger than range_leaf, else one
       // vertex task per vertex.
       const uint32_t lo = p0, hi = p1;
-      const uint32_t leaf = static_cast<uint32_t>(job_arg(p, o.job, 4));
+      const uint32_t leaf = static_cast<uint32_t>(job_arg<kExt>(p, o.job, 4));
       if (hi <= lo) return;
       o.type = OUT_FORK;
       o.d[0] = lo; o.d[1] = hi;
@@ -565,9 +581,9 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
     case TK_KC_VERTEX: {
       // K(N+(v), k-1): k = 1 counts the vertex, k = 2 its out-degree, else one
       // candidate task per out-neighbour with C = N+(v).
-      const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 0));
-      const int32_t *col = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 1));
-      const uint32_t k = static_cast<uint32_t>(job_arg(p, o.job, 3));
+      const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, o.job, 0));
+      const int32_t *col = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, o.job, 1));
+      const uint32_t k = static_cast<uint32_t>(job_arg<kExt>(p, o.job, 3));
       const uint32_t v = p0;
       if (k == 1) {
         o.value = 1;
@@ -593,8 +609,8 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
     case TK_KC_CAND: {
       // K(C /\ N+(u), l): l = 1 counts the intersection, else stores it in this
       // frame's buffer and forks one child per element.
-      const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 0));
-      const int32_t *col = reinterpret_cast<const int32_t *>(job_arg(p, o.job, 1));
+      const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, o.job, 0));
+      const int32_t *col = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, o.job, 1));
       const uint32_t u = p0, l = p1;
       const int32_t *C = reinterpret_cast<const int32_t *>(pack(p2, p3));
       const uint32_t nC = p4;
@@ -645,7 +661,7 @@ GTAP_DEV uint32_t child_class(const Params &p, uint32_t job, uint32_t ckind, con
   if constexpr (kExt) {
     if constexpr ((kExt & kExtSort) != 0) {
       if (p.daq_policy == 3) {  // Cilksort: recursive 0, serial sort 1, serial merge 2
-        const uint64_t cut = job_arg(p, job, 3);
+        const uint64_t cut = job_arg<kExt>(p, job, 3);
         if (ckind == TK_SORT) return (c.p[1] <= static_cast<uint32_t>(cut) ? 1u : 0u) % p.Q;
         if (ckind == TK_MERGE) {
           const uint32_t m = c.p[1] + c.p[3];  // a pending split takes about half
@@ -663,19 +679,19 @@ GTAP_DEV uint32_t child_class(const Params &p, uint32_t job, uint32_t ckind, con
         // ranges, row tasks, a heavy edge's search and its branches in the
         // highest class
         if (ckind != TK_KS_EDGE && ckind != TK_KS_VERTEX) return p.Q - 1;
-        const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, job, 0));
+        const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, job, 0));
         const uint32_t u = c.p[0];
         const uint32_t du = static_cast<uint32_t>(rp[u + 1] - rp[u]);
         if (ckind == TK_KS_VERTEX) return bucket_of(p, du);
-        if (job_arg(p, job, 3) >= 4) {
-          const uint64_t *mat = reinterpret_cast<const uint64_t *>(job_arg(p, job, 7));
+        if (job_arg<kExt>(p, job, 3) >= 4) {
+          const uint64_t *mat = reinterpret_cast<const uint64_t *>(job_arg<kExt>(p, job, 7));
           const uint32_t W = (du + 63) / 64;
-          const uint64_t *row = mat + (job_arg(p, job, 2) + 1) + co_ld64(mat + u) + static_cast<size_t>(c.p[1]) * W;
+          const uint64_t *row = mat + (job_arg<kExt>(p, job, 2) + 1) + co_ld64(mat + u) + static_cast<size_t>(c.p[1]) * W;
           uint32_t n = 0;
           for (uint32_t w = 0; w < W; ++w) n += __popcll(co_ld64(row + w));
           return bucket_of(p, n);
         }
-        const int32_t v = reinterpret_cast<const int32_t *>(job_arg(p, job, 1))[rp[u] + c.p[1]];
+        const int32_t v = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, job, 1))[rp[u] + c.p[1]];
         const uint32_t dv = static_cast<uint32_t>(rp[v + 1] - rp[v]);
         return bucket_of(p, du < dv ? du : dv);
       }
@@ -688,7 +704,7 @@ GTAP_DEV uint32_t child_class(const Params &p, uint32_t job, uint32_t ckind, con
     }
     case 2: {  // k-clique candidate-set bound
       if (ckind == TK_KC_RANGE) return p.Q - 1;
-      const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg(p, job, 0));
+      const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, job, 0));
       if (ckind == TK_KC_VERTEX) {
         const uint32_t v = c.p[0];
         return bucket_of(p, static_cast<uint32_t>(rp[v + 1] - rp[v]));
