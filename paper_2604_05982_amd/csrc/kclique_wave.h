@@ -33,6 +33,97 @@
 #include "wave.h"
 
 namespace gtap {
+
+// Candidate tasks of the plain k-clique search (kEmitCand): C /\ N+(u) of every
+// lane in `todo`, counted for the last level, else also written, in order, to
+// the lane's frame for its children.  The lanes' candidates are one
+// concatenated stream, 256 at a time: one device-coherent load each (they may
+// be another wavefront's writes), then a bisection of N+(u), which is read-only
+// input and served by the caches, with four searches @@GTAP_DEV void run_cands(const Params &p, uint32_t *mark, uint64_t todo, uint32_t tid, Outcome &o) {
+  constexpr uint32_t kFlight = 4;  // 64-candidate chunks in flight
+  const uint32_t ln = lane_id();
+  const bool mine = ((todo >> ln) & 1u) != 0;
+  const uint32_t n = mine && o.d[5] > 0 ? o.d[4] : 0u;
+  const uint32_t left = o.nchild;  // levels left; 1: count only
+  uint64_t dst = 0;
+  if (n > 0 && left > 1) dst = reinterpret_cast<uint64_t>(frame_ptr(p, tid) + FW_BUF);
+  uint32_t total = 0;
+  const uint32_t off = wave_exclusive_scan(n, &total);
+  const uint32_t d0 = o.d[0], d1 = o.d[1], d2 = o.d[2], d3 = o.d[3], nb = mine ? o.d[5] : 0u;
+  uint32_t longest = nb;
+  for (uint32_t i = 1; i < kWave; i <<= 1) {
+    const uint32_t y = static_cast<uint32_t>(__shfl_xor(static_cast<int>(longest), static_cast<int>(i), 64));
+    longest = y > longest ? y : longest;
+  }
+  longest = uniform(longest);
+  auto from = [](uint32_t x, uint32_t k) {
+    return static_cast<uint32_t>(__shfl(static_cast<int>(x), static_cast<int>(k), 64));
+  };
+  uint32_t carry = 0, found = 0;
+  for (uint32_t c0 = 0; c0 < total; c0 += kFlight * kWave) {
+    uint32_t own[kFlight], at[kFlight], len[kFlight];
+    int32_t x[kFlight];
+    const int32_t *list[kFlight];
+#pragma unroll
+    for (uint32_t q = 0; q < kFlight; ++q) {
+      const uint32_t g0 = c0 + q * kWave;
+      own[q] = chunk_owner(mark, n, off, g0, carry);
+      const uint64_t C = pack(from(d0, own[q]), from(d1, own[q]));
+      list[q] = reinterpret_cast<const int32_t *>(pack(from(d2, own[q]), from(d3, own[q])));
+      const uint32_t first = from(off, own[q]), nu = from(nb, own[q]);
+      const bool act = g0 + ln < total;
+      len[q] = act ? nu : 0u;
+      at[q] = 0;
+      x[q] = act ? co_ld32i(reinterpret_cast<const int32_t *>(C) + (g0 + ln - first)) : 0;
+    }
+    // at[q]: elements of the list below x[q]
+    for (uint32_t step = 1u << (31 - __builtin_clz(longest)); step > 0; step >>= 1) {
+      int32_t y[kFlight];
+#pragma unroll
+      for (uint32_t q = 0; q < kFlight; ++q) y[q] = at[q] + step <= len[q] ? list[q][at[q] + step - 1] : 0x7FFFFFFF;
+#pragma unroll
+      for (uint32_t q = 0; q < kFlight; ++q) at[q] += at[q] + step <= len[q] && y[q] < x[q] ? step : 0u;
+    }
+    bool hit[kFlight];
+#pragma unroll
+    for (uint32_t q = 0; q < kFlight; ++q) {
+      const int32_t y = at[q] < len[q] ? list[q][at[q]] : 0;
+      hit[q] = at[q] < len[q] && y == x[q];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kFlight; ++q) {
+      const uint32_t g0 = c0 + q * kWave;
+      const uint64_t m = ballot(hit[q]);
+      if (m == 0ull) continue;
+      const uint64_t buf = pack(from(static_cast<uint32_t>(dst), own[q]), from(static_cast<uint32_t>(dst >> 32), own[q]));
+      const uint32_t first = from(off, own[q]), before = from(found, own[q]);
+      const uint32_t s0 = first > g0 ? first - g0 : 0u;  // the run's first position in the chunk
+      if (hit[q] && buf != 0)
+        co_st32i(reinterpret_cast<int32_t *>(buf) + before + rank_below(m & ~((1ull << s0) - 1)), x[q]);
+      // this lane's run in the chunk: positions [a, b)
+      const uint32_t a = off > g0 ? off - g0 : 0u, b = off + n > g0 ? off + n - g0 : 0u;
+      if (a < b && a < kWave) {
+        const uint64_t run = (b >= kWave ? ~0ull : (1ull << b) - 1) & ~((1ull << a) - 1);
+        found += __popcll(m & run);
+      }
+    }
+  }
+  if (!mine) return;
+  if (left == 1) {
+    o.value = found;
+    return;
+  }
+  o.words += found;  // the candidates written for the children
+  if (found == 0) return;
+  o.type = OUT_FORK;
+  o.nchild = found;
+  o.ckind = TK_KC_CAND;
+  o.big = (left - 1 >= 2) ? 1u : 0u;
+  o.d[0] = static_cast<uint32_t>(dst); o.d[1] = static_cast<uint32_t>(dst >> 32);
+  o.d[2] = found; o.d[3] = left - 1;
+  o.d[4] = 0; o.d[5] = 0;
+}
+
 namespace kcw {
 
 constexpr uint32_t kStageWords = 2304;           // 384 out-neighbours; with the 256-entry task stack the group's LDS is full

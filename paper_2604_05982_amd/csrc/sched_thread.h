@@ -781,6 +781,11 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
   const uint32_t wv = threadIdx.x >> 6;
   WaveLds &L = lds_all[wv];
   uint4 *lstk = lstk_all[wv];
+  // several queues: the private stack is not in use, and its room keeps the
+  // first payload word of each child from the counting pass to the build pass
+  // (a k-clique candidate's vertex is a device-coherent read)
+  uint32_t *cands = reinterpret_cast<uint32_t *>(lstk);
+  constexpr uint32_t kCandCache = 8 * LC < kClassCache ? 8 * LC : kClassCache;
   uint32_t lbot = 0, ltop = 0;  // wave-uniform: entries [lbot, ltop) mod LC, newest at ltop - 1
   const uint32_t me = blockIdx.x * WPB + wv;
   const uint32_t ln = lane_id();
@@ -1030,7 +1035,7 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
     o.first = 0;
     o.words = 0;
     for (int i = 0; i < 6; ++i) o.d[i] = 0;
-    if constexpr (kExt) o.emit = 0;
+    o.emit = 0;
     if (ln < cnt) {
       TaskImage img;
       if (tid == kNone) {
@@ -1077,6 +1082,8 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
       if (m_vertex != 0ull) kcw::run_vertices(K, p.jobs, m_vertex, o.job, o.d[1], o.d[2], o.value, o.words);
       if (m_search != 0ull) kcw::run_search(p, K, m_search, tid, o);
     }
+    // k-clique candidate tasks: the lanes' intersections, by the whole wavefront
+    if (const uint64_t m_cand = ballot(o.emit == kEmitCand); m_cand != 0ull) run_cands(p, L.mark, m_cand, tid, o);
     data_words += o.words;
     const uint32_t nfirst = __popcll(ballot(o.first != 0));
     wc.add(ST_TASKS, nfirst);
@@ -1218,9 +1225,11 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
           const ForkDesc dsc = L.desc[own];
           const Words<6> d = fork_words(dsc);
           ChildInit ci;
+          const uint64_t arg0 = p.daq_policy == 2 ? job_arg<kExt>(p, dsc.job, 0) : 0;
           make_child<kExt>(dsc.ckind_big_d5 & 0x7Fu, d, g - own_off, ci);
-          c = child_class<kExt>(p, dsc.job, dsc.ckind_big_d5 & 0x7Fu, ci);
+          c = child_class<kExt>(p, dsc.job, arg0, dsc.ckind_big_d5 & 0x7Fu, ci);
           if (g < kClassCache) L.cls[g] = static_cast<uint8_t>(c);
+          if (g < kCandCache) cands[g] = ci.p[0];
         }
         for (uint32_t qq = 0; qq < p.Q; ++qq) {
           const uint32_t k = __popcll(ballot(c == qq));
@@ -1349,8 +1358,12 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
         j = g - own_off;
         dsc = L.desc[own];
         const Words<6> d = fork_words(dsc);
-        make_child<kExt>(dsc.ckind_big_d5 & 0x7Fu, d, j, ci);
-        if (p.Q > 1) c = g < kClassCache ? L.cls[g] : child_class<kExt>(p, dsc.job, dsc.ckind_big_d5 & 0x7Fu, ci);
+        make_child<kExt>(dsc.ckind_big_d5 & 0x7Fu, d, j, ci, p.Q > 1 && g < kCandCache ? cands + g : nullptr);
+        if (p.Q > 1) {
+          c = g < kClassCache ? L.cls[g]
+                              : child_class<kExt>(p, dsc.job, p.daq_policy == 2 ? job_arg<kExt>(p, dsc.job, 0) : 0,
+                                                  dsc.ckind_big_d5 & 0x7Fu, ci);
+        }
       }
       const bool big = act && (dsc.ckind_big_d5 & 0x80u);
       // rank of this child within its class

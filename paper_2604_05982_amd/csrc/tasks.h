@@ -63,7 +63,8 @@ struct Outcome {
   uint32_t first;    // 1: first execution (resume point 0), 0: continuation
   uint32_t emit;     // FMM list traversal: 1 = M2L pair, 2 = P2P pair (d[0], d[1]), descriptor d[3..4];
                      // kEmitSort / kEmitMerge: source addresses d[0..1], d[2..3], key counts d[4], d[5],
-                     // destination address (nchild, ckind); kEmitRow .. kEmitClear: split k-clique
+                     // destination address (nchild, ckind); kEmitRow .. kEmitClear: split k-clique;
+                     // kEmitCand: addresses d[0..1], d[2..3], list lengths d[4], d[5], levels left nchild
   uint32_t pc_next;  // OUT_FORK of the extended kinds: resume point after the join (Cilksort sorts fork twice)
   uint32_t words;    // 4-byte words of task data the body read or wrote (k-clique lists), for the byte count
 };
@@ -127,79 +128,6 @@ GTAP_DEV uint32_t uts_children(uint64_t id, uint32_t depth, uint64_t thr, uint32
     if (!a2) return c + 2;
     if (!a3) return c + 3;
   }
-}
-
-// First index in the ascending list b[lo, nb) whose element is >= x, by a
-// galloping search (doubling steps from lo, then bisection), and in *v that
-// element (when the index is below nb: every candidate for the answer was
-// loaded on the way, so the caller needs no second load of it); kCo: b is
-// read coherently (a buffer another wavefront wrote).
-template <bool kCo>
-GTAP_DEV int32_t ld_list(const int32_t *b, uint32_t i) {
-  if constexpr (kCo) return co_ld32i(b + i);
-  else return b[i];
-}
-template <bool kCo>
-GTAP_DEV uint32_t gallop_list(const int32_t *b, uint32_t lo, uint32_t nb, int32_t x, int32_t *v) {
-  if (lo >= nb) return nb;
-  const int32_t y = ld_list<kCo>(b, lo);
-  if (y >= x) {
-    *v = y;
-    return lo;
-  }
-  uint32_t step = 1, prev = lo;
-  int32_t vh = 0;
-  while (prev + step < nb) {
-    const int32_t t = ld_list<kCo>(b, prev + step);
-    if (t >= x) {
-      vh = t;
-      break;
-    }
-    prev += step;
-    step <<= 1;
-  }
-  uint32_t l = prev + 1, h = prev + step < nb ? prev + step : nb;
-  while (l < h) {
-    const uint32_t mid = l + (h - l) / 2;
-    const int32_t t = ld_list<kCo>(b, mid);
-    if (t < x) {
-      l = mid + 1;
-    } else {
-      h = mid;
-      vh = t;
-    }
-  }
-  *v = vh;
-  return l;
-}
-// Common elements of the ascending lists s (walked) and l (galloped into);
-// the next element of s is loaded while the current one's search runs.
-template <bool kCoS, bool kCoL>
-GTAP_DEV uint32_t isect_gallop(const int32_t *s, uint32_t ns, const int32_t *l, uint32_t nl, int32_t *out) {
-  uint32_t j = 0, o = 0;
-  int32_t x = ld_list<kCoS>(s, 0);
-  for (uint32_t i = 0; i < ns && j < nl; ++i) {
-    const int32_t xn = i + 1 < ns ? ld_list<kCoS>(s, i + 1) : 0;
-    int32_t v = 0;
-    j = gallop_list<kCoL>(l, j, nl, x, &v);
-    if (j < nl && v == x) {
-      if (out) co_st32i(out + o, x);
-      ++o;
-      ++j;
-    }
-    x = xn;
-  }
-  return o;
-}
-
-// |C /\ B| for an ascending candidate list C (read coherently: it may be a
-// buffer another wavefront wrote) and an ascending CSR list B (read-only
-// input); writes the intersection coherently if out != 0.  The shorter list
-// is walked and each of its elements galloped to in the longer one.
-GTAP_DEV uint32_t intersect_sorted(const int32_t *C, uint32_t nc, const int32_t *B, uint32_t nb,
-                                   int32_t *out) {
-  if (nc == 0 || nb == 0) return 0;
-  return nc <= nb ? isect_gallop<true, false>(C, nc, B, nb, out) : isect_gallop<false, true>(B, nb, C, nc, out);
 }
 
 // Job arguments.  While serving, a job slot is rewritten by the wave that admits
@@ -285,6 +213,7 @@ GTAP_DEV uint32_t count_below(const uint32_t *s, uint32_t n, const uint32_t *pv)
 constexpr uint32_t kEmitRow = 5;     // one row of a vertex's matrix
 constexpr uint32_t kEmitVertex = 6;  // a vertex counted in place: d[1] = first out-list position, d[2] = out-degree
 constexpr uint32_t kEmitSearch = 7;  // an edge, a heavy edge's root or a branch
+constexpr uint32_t kEmitCand = 9;    // a candidate task: C /\ N+(u)
 constexpr uint32_t kEmitClear = 8;   // pivoting: a vertex about to fork row tasks, whose U is cleared first
 
 // Edge (u, i), k = 3: |N+(u) /\ N+(v)|, v = the i-th out-neighbour of u.
@@ -611,27 +540,16 @@ GTAP_DEV void exec_task(const Params &p, uint32_t tid, const TaskImage &img, Out
       // frame's buffer and forks one child per element.
       const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, o.job, 0));
       const int32_t *col = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, o.job, 1));
-      const uint32_t u = p0, l = p1;
-      const int32_t *C = reinterpret_cast<const int32_t *>(pack(p2, p3));
-      const uint32_t nC = p4;
-      const int32_t s = rp[u], e = rp[u + 1];
-      const uint32_t nu = static_cast<uint32_t>(e - s);
-      o.words = 2 + nC + nu;  // row bounds, the parent's candidates, N+(u)
-      if (l == 1) {
-        o.value = intersect_sorted(C, nC, col + s, nu, nullptr);
-        return;
-      }
-      int32_t *buf = reinterpret_cast<int32_t *>(f + FW_BUF);
-      const uint32_t m = intersect_sorted(C, nC, col + s, nu, buf);
-      o.words += m;  // the candidates written for the children
-      if (m == 0) return;
-      const uint64_t cptr = reinterpret_cast<uint64_t>(buf);
-      o.type = OUT_FORK;
-      o.nchild = m;
-      o.ckind = TK_KC_CAND;
-      o.big = (l - 1 >= 2) ? 1u : 0u;
-      o.d[0] = static_cast<uint32_t>(cptr); o.d[1] = static_cast<uint32_t>(cptr >> 32);
-      o.d[2] = m; o.d[3] = l - 1;
+      // (described here; the wavefront runs its lanes' intersections together)
+      const int32_t s = rp[p0], e = rp[p0 + 1];
+      const uint64_t nu = reinterpret_cast<uint64_t>(col + s);
+      o.emit = kEmitCand;
+      o.d[0] = p2; o.d[1] = p3;  // C
+      o.d[2] = static_cast<uint32_t>(nu); o.d[3] = static_cast<uint32_t>(nu >> 32);
+      o.d[4] = p4;
+      o.d[5] = static_cast<uint32_t>(e - s);
+      o.nchild = p1;
+      o.words = 2 + o.d[4] + o.d[5];  // row bounds, the parent's candidates, N+(u)
       return;
     }
     default:
@@ -655,8 +573,9 @@ GTAP_DEV uint32_t bucket_of(const Params &p, uint32_t x) {
 // of its intersection and thus on its cost; a vertex task by its out-degree
 // (its candidate set is N+(v)); a vertex-range task, whose subtree spans many
 // vertices, by the highest class.
+// (arg0: job argument 0, read by the caller for that policy.)
 template <uint32_t kExt = 0>
-GTAP_DEV uint32_t child_class(const Params &p, uint32_t job, uint32_t ckind, const ChildInit &c) {
+GTAP_DEV uint32_t child_class(const Params &p, uint32_t job, uint64_t arg0, uint32_t ckind, const ChildInit &c) {
   if (p.Q <= 1) return 0;
   if constexpr (kExt) {
     if constexpr ((kExt & kExtSort) != 0) {
@@ -704,7 +623,7 @@ GTAP_DEV uint32_t child_class(const Params &p, uint32_t job, uint32_t ckind, con
     }
     case 2: {  // k-clique candidate-set bound
       if (ckind == TK_KC_RANGE) return p.Q - 1;
-      const int32_t *rp = reinterpret_cast<const int32_t *>(job_arg<kExt>(p, job, 0));
+      const int32_t *rp = reinterpret_cast<const int32_t *>(arg0);
       if (ckind == TK_KC_VERTEX) {
         const uint32_t v = c.p[0];
         return bucket_of(p, static_cast<uint32_t>(rp[v + 1] - rp[v]));
@@ -725,9 +644,9 @@ GTAP_DEV uint32_t nth_set_bit(uint32_t m, uint32_t j) {
 }
 
 // Payload of child j of a forked parent with child kind `ckind` and
-// descriptor d.
+// descriptor d (cand: a k-clique candidate child's vertex, if it was read before).
 template <uint32_t kExt = 0>
-GTAP_DEV void make_child(uint32_t ckind, const Words<6> &d, uint32_t j, ChildInit &c) {
+GTAP_DEV void make_child(uint32_t ckind, const Words<6> &d, uint32_t j, ChildInit &c, const uint32_t *cand = nullptr) {
   for (uint32_t i = 0; i < kPayloadWords; ++i) c.p[i] = 0;
   if constexpr (kExt) {
     if constexpr ((kExt & kExtSort) != 0) {
@@ -819,7 +738,7 @@ GTAP_DEV void make_child(uint32_t ckind, const Words<6> &d, uint32_t j, ChildIni
       break;
     case TK_KC_CAND: {
       const int32_t *C = reinterpret_cast<const int32_t *>(pack(d[0], d[1]));
-      c.p[0] = static_cast<uint32_t>(co_ld32i(C + j));
+      c.p[0] = cand != nullptr ? *cand : static_cast<uint32_t>(co_ld32i(C + j));
       c.p[1] = d[3];
       c.p[2] = d[0];
       c.p[3] = d[1];
