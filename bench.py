@@ -45,7 +45,8 @@ VALU_FILE = os.path.join(ROOT, "profiles", "thread_sched_kernel_kclique7_valu_da
 # The HIP sources each scheduler kernel is compiled from (the block-mode
 # kernel includes the thread-mode headers; the thread-mode kernel does not
 # include the block-mode one).
-THREAD_KERNEL_SOURCES = ("layout.h", "wave.h", "tasks.h", "kclique_bits.h", "sched_thread.h", "fmm.h", "fmm_lists.h")
+THREAD_KERNEL_SOURCES = ("layout.h", "wave.h", "tasks.h", "kclique_bits.h", "kclique_wave.h", "sort_wave.h",
+                         "sched_thread.h", "fmm.h", "fmm_lists.h")
 BLOCK_KERNEL_SOURCES = THREAD_KERNEL_SOURCES + ("sched_block.h",)
 
 

@@ -321,8 +321,8 @@ int gtap_submit(gtap_ctx *ctx, int32_t kind, const void *args, size_t args_bytes
 /* Launch one persistent kernel for every pending job on cfg->stream and wait
  * for it.  Jobs' results become readable with gtap_result.  FMM jobs also run
  * their tree construction and upward pass before, and their downward pass
- * after, that launch (device memory for them is allocated and freed inside
- * this call).  Returns GTAP_E_CAPACITY or GTAP_E_TIMEOUT when the device
+ * after, that launch (device memory for them is allocated inside this call
+ * and kept by the context for its next runs, up to 8 GB).  Returns GTAP_E_CAPACITY or GTAP_E_TIMEOUT when the device
  * aborted the run (results of that run are then invalid; the context stays
  * usable), GTAP_E_INVAL when an FMM job's points leave the root cube,
  * GTAP_E_NOMEM, GTAP_E_HIP on a HIP failure. */

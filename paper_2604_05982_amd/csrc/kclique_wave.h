@@ -10,8 +10,9 @@
 // orientation: 64 rows 582 k cycles, 64 edges 801 k, 64 branches 509 k, 64
 // vertices in place 2.2 M; VALU lane utilisation 23 %): 88 ms per call, this way
 // 36 ms (rows 247 k, edges and branches 160 k, vertices in place 1.0 M; all
-// now bound by load and LDS latency with one wavefront per SIMD).  100,003
-// vertices, mean degree 30, k = 6, pivoting: 17-21 -> 6.6 ms.
+// now bound by load and LDS latency with one wavefront per SIMD), 28 ms with
+// the scheduler of today.  100,003 vertices, mean degree 30, k = 6, pivoting:
+// 17-21 -> 6.6 -> 5.3 ms.
 //
 //   rows (and the rows of vertices in place): row i holds members after the
 //     i-th only, so either the rest of N+(u) is searched in N+(x) or N+(x) in

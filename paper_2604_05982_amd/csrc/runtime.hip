@@ -275,8 +275,12 @@ struct DevCache {
     }
     void *p = nullptr;
     if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();  // or the next launch check would report it
       trim(0);  // unused buffers first
-      if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+      if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
     }
     bufs.push_back(Buf{p, bytes, true});
     return p;

@@ -9,7 +9,7 @@
 // merge of 256 keys is 256 dependent steps, each about a microsecond, on one
 // lane).  100,003 keys on one queue: 6.7 ms in the kernel lane-serially, 3.1 ms
 // this way (1.8 ms with tasks exposed early); 30 M keys on three queues: 26.6 ->
-// 12.6 ms.
+// 13.1 ms (9.2 ms with fresh frames claimed by one add).
 //
 // Both run as bitonic networks on registers: partners at lane distance 1..8
 // come by DPP, 16 and 32 by the row-swap instructions, 64 and 128 are other
