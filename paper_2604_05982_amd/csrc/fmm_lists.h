@@ -220,21 +220,38 @@ __global__ void k_list_segments(const uint64_t *pairs, uint64_t n, uint64_t *lo,
 }
 
 // Order-independent wrapping sum of pair hashes of a list (the oracle's check)
-// and the number of real pairs (gaps, target == ncells, are skipped).
-__global__ __launch_bounds__(256) void k_list_hash(const uint64_t *pairs, uint64_t n, uint32_t ncells, uint64_t *out,
-                                                   uint64_t *count) {
+// and the number of real pairs (gaps, target == ncells, are skipped).  Bound by
+// reading the list; the device adds to one word only 0.083 G times a second,
+// so a workgroup of 1,024 threads sums first and the grid is one per compute
+// unit (an add per wavefront of 4,096: 102 us for a list of any length).
+constexpr uint32_t kHashThreads = 1024, kHashBlocks = 256;
+__global__ __launch_bounds__(kHashThreads) void k_list_hash(const uint64_t *__restrict__ pairs, uint64_t n,
+                                                            uint32_t ncells, uint64_t *out, uint64_t *count) {
+  __shared__ uint64_t sum[2][kHashThreads / kWave];
   uint64_t h = 0, k = 0;
-  for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
-    const uint32_t a = static_cast<uint32_t>(pairs[i] >> 32);
-    if (a >= ncells) continue;
-    h += pair_hash(a, static_cast<uint32_t>(pairs[i]));
-    ++k;
+#pragma unroll 4
+  for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kHashThreads + threadIdx.x; i < n;
+       i += static_cast<uint64_t>(gridDim.x) * kHashThreads) {
+    const uint64_t e = pairs[i];
+    const uint32_t a = static_cast<uint32_t>(e >> 32);
+    const uint64_t x = pair_hash(a, static_cast<uint32_t>(e));
+    h += a < ncells ? x : 0;
+    k += a < ncells ? 1 : 0;
   }
   h = readlane64(wave_inclusive_sum64(h), 63);
   k = readlane64(wave_inclusive_sum64(k), 63);
-  if (lane_id() == 0 && h) fetch_add_relaxed(out, h);
-  if (lane_id() == 0 && k) fetch_add_relaxed(count, k);
+  const uint32_t wv = threadIdx.x / kWave, ln = lane_id();
+  if (ln == 0) {
+    sum[0][wv] = h;
+    sum[1][wv] = k;
+  }
+  __syncthreads();
+  if (wv != 0) return;
+  const bool act = ln < kHashThreads / kWave;
+  h = readlane64(wave_inclusive_sum64(act ? sum[0][ln] : 0), 63);
+  k = readlane64(wave_inclusive_sum64(act ? sum[1][ln] : 0), 63);
+  if (ln == 0 && h) fetch_add_relaxed(out, h);
+  if (ln == 0 && k) fetch_add_relaxed(count, k);
 }
 
 // 1 / sqrt(x) for x > 0: the hardware estimate y (relative error below 2^-23)

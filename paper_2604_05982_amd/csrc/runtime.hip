@@ -1138,7 +1138,7 @@ int fmm_eval_lists(gtap_ctx *c, FmmJobMem &m, uint64_t n_m2l, uint64_t n_p2p, gt
       return GTAP_E_HIP;
     hipLaunchKernelGGL(fmm::k_list_segments, dim3(nblk(static_cast<int64_t>(cnt), 256)), dim3(256), 0, st, m.sorted,
                        cnt, lo, hi);
-    hipLaunchKernelGGL(fmm::k_list_hash, dim3(1024), dim3(256), 0, st, m.sorted, cnt,
+    hipLaunchKernelGGL(fmm::k_list_hash, dim3(fmm::kHashBlocks), dim3(fmm::kHashThreads), 0, st, m.sorted, cnt,
                        static_cast<uint32_t>(m.ncells), hash, pairs);
     return GTAP_OK;
   };
