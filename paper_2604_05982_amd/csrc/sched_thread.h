@@ -201,18 +201,24 @@ GTAP_DEV bool depot_refill(PoolView &P, uint32_t me, bool all, WaveCounters &wc)
 // With room to spare the claim is one add: a compare-and-swap loop lets one of
 // the contending wavefronts through per round trip (1 to 2 us), which held
 // jobs that keep touching new frames to that rate (k-clique tasks on 300,000
-// vertices, 4.3 M frames: 23 k of an iteration's 56 k cycles).  An add that
-// passes the end after all is taken back; until then the word exceeds the
-// pool's size, and whoever reads such a value reads again.
+// vertices, 4.3 M frames: 23 k of an iteration's 56 k cycles).
+//
+// A value up to the pool's size is always the number of frames handed out.  An
+// add may pass the end after all, since others claim between the load and the
+// add.  The one that takes the word from there past the end puts back what it
+// found, with an exchange; until it does the word exceeds the pool's size,
+// every other add finds it so and changes nothing that lasts, and whoever sees
+// such a value reads again.  (Subtracting instead would leave the other failed
+// adds in a value that looks valid, and hand out frames twice.)
 GTAP_DEV uint32_t bump_claim(const Params &p, const PoolView &P, uint32_t n) {
-  constexpr uint32_t kMargin = 512;  // frames per wavefront, more than one claim takes
+  constexpr uint32_t kMargin = 512;  // frames per wavefront, more than most claims take: passing the end is rare
   uint32_t base = kNone;
   if (lane_id() == 0) {
     uint64_t cur = ld_relaxed(P.bump);
     if (cur + n + static_cast<uint64_t>(p.nwaves) * kMargin <= P.nframes) {
       cur = fetch_add_relaxed(P.bump, static_cast<uint64_t>(n));
       if (cur + n <= P.nframes) base = static_cast<uint32_t>(cur);
-      else cur = fetch_add_relaxed(P.bump, ~static_cast<uint64_t>(n) + 1) - n;
+      else if (cur <= P.nframes) (void)exchange_relaxed(P.bump, cur);
     }
     while (base == kNone && (cur + n <= P.nframes || cur > P.nframes)) {
       if (cur > P.nframes) cur = ld_relaxed(P.bump);
