@@ -78,6 +78,7 @@ enum TaskKind : uint32_t {
 constexpr uint32_t kExtLists = 1;  // FMM list-building cell pairs
 constexpr uint32_t kExtSplit = 2;  // k-clique with bitset candidate subgraphs (TK_KS_*)
 constexpr uint32_t kExtSort = 4;   // Cilksort sorts and merges
+constexpr uint32_t kExtShort = 8;  // with kExtSort: short ranges share registers (not needed for correctness)
 constexpr uint32_t kExtAll = kExtLists | kExtSplit | kExtSort;
 
 struct alignas(128) DequeMeta {

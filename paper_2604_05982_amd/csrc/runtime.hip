@@ -791,12 +791,16 @@ static int launch_sched(gtap_ctx *c, uint32_t ext = 0) {
           break;
         default:
           // the smallest compiled extension set that has the batch's kinds
+          if (ext != (kExtSort | kExtShort)) ext &= ~kExtShort;
           if (ext == 0)
             hipLaunchKernelGGL(thread_sched_kernel<4>, grid, block, 0, c->stream, c->params);
           else if (ext == kExtLists)
             hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtLists>), grid, block, 0, c->stream, c->params);
           else if (ext == kExtSort)
             hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtSort>), grid, block, 0, c->stream, c->params);
+          else if (ext == (kExtSort | kExtShort))
+            hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtSort | kExtShort>), grid, block, 0, c->stream,
+                               c->params);
           else if (ext == kExtSplit)
             hipLaunchKernelGGL((thread_sched_kernel<4, kSchedBatched, kExtSplit>), grid, block, 0, c->stream, c->params);
           else if (ext == (kExtLists | kExtSort))
@@ -1226,7 +1230,11 @@ int gtap_run(gtap_ctx *c) {
   for (size_t j = 0; j < nj; ++j) {
     any_fmm |= c->pending[j].kind == GTAP_KIND_FMM;
     if (c->pending[j].kind == GTAP_KIND_FMM) ext |= kExtLists;
-    if (c->pending[j].kind == GTAP_KIND_CILKSORT) ext |= kExtSort;
+    if (c->pending[j].kind == GTAP_KIND_CILKSORT) {
+      // cutoffs whose ranges leave most of a register or a merge tile empty (sort_wave.h)
+      const uint64_t cut = c->pending[j].a[3];
+      ext |= kExtSort | (static_cast<uint32_t>(cut) <= 32 || (cut >> 32) <= 64 ? kExtShort : 0u);
+    }
     if (c->pending[j].kind == GTAP_KIND_KCLIQUE_SPLIT) ext |= kExtSplit;
   }
   std::vector<void *> ks_mem;

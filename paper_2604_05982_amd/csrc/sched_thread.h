@@ -779,7 +779,8 @@ struct LocalCap {
 // kSchedBatchedNoLocal = batched without the private stack) at compile time,
 // so the comparison variants add nothing to the scheduler as designed; kExt
 // adds extension task sets (kExtLists: the FMM list-building cell pairs and
-// their list appends; kExtSort: Cilksort; kExtSplit: split k-clique).
+// their list appends; kExtSort: Cilksort, with kExtShort its small cutoffs;
+// kExtSplit: split k-clique).
 template <int WPB, uint32_t V = kSchedBatched, uint32_t kExt = 0>
 __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
   constexpr bool kCentral = (V == kSchedCentral);
@@ -1078,7 +1079,12 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
     }
     if constexpr ((kExt & kExtSort) != 0) {
       // Cilksort: the lanes' serial sorts and merges, by the whole wavefront
-      const uint64_t m_sort = ballot(o.emit == kEmitSort), m_merge = ballot(o.emit == kEmitMerge);
+      uint64_t m_sort = ballot(o.emit == kEmitSort), m_merge = ballot(o.emit == kEmitMerge);
+      if constexpr ((kExt & kExtShort) != 0) {
+        const cilk::Desc d{{o.d[0], o.d[1]}, {o.d[2], o.d[3]}, {o.nchild, o.ckind}, o.d[4], o.d[5]};
+        if (m_sort != 0ull && cilk::run_short_sorts(m_sort, d)) m_sort = 0;
+        if (m_merge != 0ull && cilk::run_short_merges(m_merge, d)) m_merge = 0;
+      }
       auto span_of = [&](int k) {
         return cilk::Span{reinterpret_cast<const uint32_t *>(cilk::lane_u64(o.d[0], o.d[1], k)),
                           reinterpret_cast<const uint32_t *>(cilk::lane_u64(o.d[2], o.d[3], k)),

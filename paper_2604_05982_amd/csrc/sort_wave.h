@@ -16,6 +16,15 @@
 // registers, so a network touches no LDS.  A tile of 256 keys needs 8 rounds
 // on 4 registers (about 80 instructions); the loads of the next tiles are
 // issued before a network runs, which hides most of their latency.
+//
+// Sorts of at most 32 keys and merges of at most 64 would leave most of a
+// register's lanes or of a tile empty, at the same number of rounds: with small
+// cutoffs that was slower than the lane-serial form.  They share registers
+// instead, 64 / W ranges of at most W keys side by side: 1 M keys with cutoffs
+// 8 and 16: 10.3 ms lane-serially, 16.4 ms a range at a time, 8.2 ms this way;
+// cutoffs 64 and 64: 12.7, 9.3 and 6.8 ms.  The bodies for that are compiled
+// into a kernel of their own (kExtShort): in the other one they cost sorts with
+// the default cutoffs 1 to 2 %.
 #pragma once
 #include "wave.h"
 
@@ -59,14 +68,11 @@ GTAP_DEV void merge_round(uint32_t (&x)[N]) {
 #pragma unroll
   for (uint32_t i = 0; i < N; ++i) x[i] = exchange<D>(x[i], low);
 }
-template <uint32_t N>
-GTAP_DEV void merge_lanes(uint32_t (&x)[N]) {
-  merge_round<32>(x);
-  merge_round<16>(x);
-  merge_round<8>(x);
-  merge_round<4>(x);
-  merge_round<2>(x);
-  merge_round<1>(x);
+// Ascending order of bitonic sequences over 2 D lanes each.
+template <int D, uint32_t N>
+GTAP_DEV void merge_from(uint32_t (&x)[N]) {
+  merge_round<D>(x);
+  if constexpr (D > 1) merge_from<D / 2>(x);
 }
 
 // One round of the sort's stage K (sorted runs of K lanes, alternating
@@ -84,15 +90,15 @@ GTAP_DEV void sort_stage(uint32_t (&x)[N]) {
   if constexpr (D > 1) sort_stage<K, D / 2>(x);
 }
 
-// Sort each register's 64 keys over the lanes, ascending.
-template <uint32_t N>
+// Sort each W keys of a register over their lanes, ascending.
+template <int W, int K = 2, uint32_t N>
 GTAP_DEV void sort_lanes(uint32_t (&x)[N]) {
-  sort_stage<2, 1>(x);
-  sort_stage<4, 2>(x);
-  sort_stage<8, 4>(x);
-  sort_stage<16, 8>(x);
-  sort_stage<32, 16>(x);
-  merge_lanes(x);
+  if constexpr (K < W) {
+    sort_stage<K, K / 2>(x);
+    sort_lanes<W, 2 * K>(x);
+  } else {
+    merge_from<W / 2>(x);
+  }
 }
 
 // Ascending order of a bitonic sequence of 256 keys, key r * 64 + lane in x[r].
@@ -109,7 +115,7 @@ GTAP_DEV void merge_tile(uint32_t (&x)[kTileRegs]) {
     x[r] = a < b ? a : b;
     x[r + 1] = a < b ? b : a;
   }
-  merge_lanes(x);
+  merge_from<32>(x);
 }
 
 // A serial sort (nb unused) or merge as one lane described it; wave-uniform.
@@ -163,6 +169,69 @@ GTAP_DEV uint64_t lane_u64(uint32_t lo, uint32_t hi, int k) {
          (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hi), k))) << 32);
 }
 
+// A serial sort or merge as its lane describes it: addresses as two words.
+struct Desc {
+  uint32_t a[2], b[2], out[2], na, nb;
+};
+
+// Run the sorts (kMerge: merges) of the lanes in `m`, at most W keys each: the
+// t-th takes W lanes, 4 * 64 / W of them at a time.  The descriptions move to
+// the lanes [0, number of lanes in m) once.
+template <int W, bool kMerge>
+GTAP_DEV void run_short(uint64_t m, const Desc &d) {
+  constexpr uint32_t N = 4, S = kWave / W;
+  const uint32_t ln = lane_id(), count = static_cast<uint32_t>(__popcll(m)), i = ln % W;
+  const int to = static_cast<int>(4 * ((m >> ln) & 1u ? rank_below(m) : count + rank_below(~m)));
+  auto move = [&](uint32_t x) {
+    return static_cast<uint32_t>(__builtin_amdgcn_ds_permute(to, static_cast<int>(x)));
+  };
+  const Desc g{{move(d.a[0]), move(d.a[1])}, {kMerge ? move(d.b[0]) : 0u, kMerge ? move(d.b[1]) : 0u},
+               {move(d.out[0]), move(d.out[1])}, move(d.na), kMerge ? move(d.nb) : 0u};
+  for (uint32_t t0 = 0; t0 < count; t0 += N * S) {
+    uint32_t *out[N];
+    uint32_t len[N], x[N];
+#pragma unroll
+    for (uint32_t q = 0; q < N; ++q) {
+      const uint32_t t = t0 + q * S + ln / W;
+      auto of = [&](uint32_t v) {
+        return static_cast<uint32_t>(__shfl(static_cast<int>(v), static_cast<int>(t % kWave), 64));
+      };
+      auto ptr = [&](const uint32_t (&w)[2]) {
+        return reinterpret_cast<uint32_t *>(of(w[0]) | (static_cast<uint64_t>(of(w[1])) << 32));
+      };
+      const uint32_t *a = ptr(g.a), *b = kMerge ? ptr(g.b) : nullptr;
+      const uint32_t na = of(g.na), nb = kMerge ? of(g.nb) : 0u;
+      out[q] = ptr(g.out);
+      len[q] = t < count ? na + nb : 0u;
+      x[q] = kPad;
+      if (t < count) {
+        if (i < na) x[q] = co_ld32(a + i);
+        else if (W - 1 - i < nb) x[q] = co_ld32(b + (W - 1 - i));
+      }
+    }
+    if constexpr (kMerge) merge_from<W / 2>(x);
+    else sort_lanes<W>(x);
+#pragma unroll
+    for (uint32_t q = 0; q < N; ++q)
+      if (i < len[q]) co_st32(out[q] + i, x[q]);
+  }
+}
+
+// The sorts or merges of the lanes in `m` that way, if all of them are short.
+// (Widths of 16 for sorts and 32 for merges as well measured the same.)
+GTAP_DEV bool run_short_sorts(uint64_t m, const Desc &d) {
+  if ((ballot(d.na > 32) & m) != 0ull) return false;
+  if ((ballot(d.na > 8) & m) == 0ull) run_short<8, false>(m, d);
+  else run_short<32, false>(m, d);
+  return true;
+}
+GTAP_DEV bool run_short_merges(uint64_t m, const Desc &d) {
+  if ((ballot(d.na + d.nb > 64) & m) != 0ull) return false;
+  if ((ballot(d.na + d.nb > 16) & m) == 0ull) run_short<16, true>(m, d);
+  else run_short<64, true>(m, d);
+  return true;
+}
+
 // Run the serial sorts of the lanes in `m` (span_of(k): lane k's).  Four at a
 // time keep the DPP chains of one network apart and four loads in flight;
 // the next four are loaded before the current ones are sorted.
@@ -191,7 +260,7 @@ GTAP_DEV void run_sorts(uint64_t m, SpanFn span_of) {
   for (;;) {
     const bool more = rest != 0;
     if (more) load(nxt, y);
-    sort_lanes(x);
+    sort_lanes<64>(x);
 #pragma unroll
     for (uint32_t i = 0; i < N; ++i)
       if (lane_id() < cur[i].na) co_st32(cur[i].out + lane_id(), x[i]);
