@@ -16,8 +16,8 @@
 //
 //   rows (and the rows of vertices in place): either the members of N+(u) are
 //     searched in N+(x), x the i-th of them, or N+(x) in N+(u), whichever has
-//     fewer needles; only members between N+(x)'s first and last element can
-//     be in it (where ids ascend along the edges, a part of those after x).
+//     fewer needles.  Where N+(x) begins after x (as it does for every
+//     x where ids ascend along the edges) only members after x can be in it.
 //     The needles of 64 rows are one concatenated stream, 256 at a time, so
 //     that four loads a lane are in flight and a lane's share does not depend
 //     on its own row's length;
@@ -239,20 +239,6 @@ GTAP_DEV void chunk_owners(uint32_t *mark, uint32_t pre, uint32_t len, uint32_t 
   wave_sync();
 }
 
-// Number of elements below v in the ascending list nu[0, n) (LDS; n <=
-// `longest`, wave-uniform).
-GTAP_DEV uint32_t members_below(const int32_t *nu, uint32_t n, uint32_t longest, int32_t v) {
-  uint32_t top = 1, at = 0;
-  while (top * 2 <= longest) top *= 2;
-  for (uint32_t step = top; step >= 1; step >>= 1) {
-    const uint32_t t = at + step;
-    const bool in = t <= n;
-    const int32_t y = nu[in ? t - 1 : 0u];
-    if (in && y < v) at = t;
-  }
-  return at;
-}
-
 // Walk the concatenation of the lanes' out-lists col[beg, beg + len) and
 // search every element in the ascending list nu[lo, lo + n) (LDS; n <=
 // `longest`, wave-uniform): hit(owner lane, index) for each element found.
@@ -453,15 +439,12 @@ GTAP_DEV void run_rows(Lds &S, const JobSlot *jobs, uint64_t todo, uint32_t job,
     for (uint32_t t = ln; t < static_cast<uint32_t>(__popcll(g)) * M.W; t += kWave) row[t] = 0;
     wave_sync();
     uint32_t beg = 0, len = 0;
-    int32_t least = 0, most = -1;  // N+(x)'s first and last element
+    bool before = false;  // N+(x) begins before x
     if (mine) {
       const int32_t x = nu[i];
       beg = static_cast<uint32_t>(J.rp[x]);
       len = static_cast<uint32_t>(J.rp[x + 1]) - beg;
-      if (len > 0) {
-        least = J.col[beg];
-        most = J.col[beg + len - 1];
-      }
+      if (len > 0) before = J.col[beg] < x;
       words = 4 + M.d + len + (J.pivot ? 4 : 2) * M.W;  // row bounds, both lists, the row (and U's) written
     }
     uint64_t *U = M.rows;
@@ -471,9 +454,8 @@ GTAP_DEV void run_rows(Lds &S, const JobSlot *jobs, uint64_t todo, uint32_t job,
       const uint32_t ro = static_cast<uint32_t>(__popcll(g & ((1ull << own) - 1ull)));
       lds_or(row + ro * W + (j >> 6), 1ull << (j & 63));
     };
-    // the shorter of N+(x) and N+(u)'s members within its bounds is searched in the other
-    const uint32_t first = members_below(nu, M.d, M.d, least);
-    const uint32_t rest = len > 0 ? members_below(nu, M.d, M.d, most + 1) - first : 0u;
+    // the shorter of N+(x) and the members that can be in it is searched in the other
+    const uint32_t first = before ? 0u : i + 1, rest = mine ? M.d - first : 0u;
     const bool walk = len < rest;
     if (ballot(walk) != 0ull) scan_lists(S.mark, J.col, beg, walk ? len : 0u, nu, 0u, M.d, M.d, hit);
     scan_needles(S.mark, J.col, beg, len, nu, first, walk ? 0u : rest, hit);
@@ -549,16 +531,13 @@ GTAP_DEV void run_vertices(Lds &S, const JobSlot *jobs, uint64_t todo, uint32_t 
     S.seg[ln] = seg;
     S.vtx[ln] = own;
     uint32_t beg = 0, len = 0;
-    int32_t least = 0, most = -1;
+    bool before = false;
     if (row) {
       const int32_t x = J.col[at];
       nu[ln] = x;
       beg = static_cast<uint32_t>(J.rp[x]);
       len = static_cast<uint32_t>(J.rp[x + 1]) - beg;
-      if (len > 0) {
-        least = J.col[beg];
-        most = J.col[beg + len - 1];
-      }
+      if (len > 0) before = J.col[beg] < x;
       __hip_atomic_fetch_add(&S.list[own], 2 + len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     wave_sync();
@@ -571,11 +550,10 @@ GTAP_DEV void run_vertices(Lds &S, const JobSlot *jobs, uint64_t todo, uint32_t 
         lds_or(&S.B[j], 1ull << (r - sg));
       }
     };
-    const uint32_t vs = row ? dv : 0u, before = members_below(nu + seg, vs, kWave, least);
-    const uint32_t rest = len > 0 ? members_below(nu + seg, vs, kWave, most + 1) - before : 0u;
+    const uint32_t first = before ? seg : ln + 1, rest = row ? seg + dv - first : 0u;
     const bool walk = len < rest;
-    if (ballot(walk) != 0ull) scan_lists(S.mark, J.col, beg, walk ? len : 0u, nu, seg, vs, kWave, hit);
-    scan_needles(S.mark, J.col, beg, len, nu, seg + before, walk ? 0u : rest, hit);
+    if (ballot(walk) != 0ull) scan_lists(S.mark, J.col, beg, walk ? len : 0u, nu, seg, row ? dv : 0u, kWave, hit);
+    scan_needles(S.mark, J.col, beg, len, nu, first, walk ? 0u : rest, hit);
     wave_sync();
     uint64_t a = row ? S.A[ln] : 0ull;
     if (static_cast<uint32_t>(__popcll(a)) < J.kk) a = 0ull;
