@@ -854,10 +854,9 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
 
   uint32_t idle = 0;
   uint32_t iter = 0;
-  // iterations at which exposing tasks is looked at: iter & xmask == 0 (small
-  // frame pools keep to the eighths: tasks exposed early hold frames sooner)
-  uint32_t xmask = kRamp && p.nframes_s / (kRampChecks * kWave) >= p.nwaves ? 0u : kExposeMask;
-  uint32_t ramp_left = kRampChecks;
+  // looks at exposing tasks left outside every eighth iteration (none with
+  // small frame pools: tasks exposed early hold frames sooner)
+  uint32_t ramp_left = kRamp && p.nframes_s / (kRampChecks * kWave) >= p.nwaves ? kRampChecks : 0u;
   uint32_t steal_wait = 0;  // iterations left in which this wavefront, holding tasks, does not try to steal
   bool hungry = false;  // counted in the control block's hungry-wavefront hint
   bool tcont = false;  // this lane's task is a resumed parent (runs its continuation)
@@ -1283,27 +1282,33 @@ __global__ __launch_bounds__(64 * WPB) void thread_sched_kernel(Params p) {
       const uint32_t have = ltop - lbot;
       uint32_t ex = (have + nsmall > LC) ? (have + nsmall - LC) : 0u;
       if (ex > have) ex = have;
-      if ((iter & xmask) == 0 && have >= (xmask ? 2 * kWave : kWave / 2)) {
+      const bool regular = (iter & kExposeMask) == 0 && have >= 2 * kWave;
+      const bool early = kRamp && ramp_left > 0 && have >= kWave / 2;
+      if (regular || early) {
         // half the stack goes to the deque when it runs low and some
         // wavefront is looking for work (both words read in one round trip).
-        // In its first iterations a wavefront looks at that every time and,
-        // while most of the grid is idle, exposes a batch of its oldest tasks:
-        // an iteration lasts 7 to 10 us, so waiting for the eighth kept small
-        // jobs on a few wavefronts (a sort of 100,003 keys 3.0 -> 1.8 ms, a
-        // batch of 27,518 tasks 0.64 -> 0.45 ms).  Later it would cost large
+        // In its first iterations a wavefront also looks at that every time
+        // and, while most of the grid is idle, exposes a batch of its oldest
+        // tasks: an iteration lasts 7 to 10 us, so waiting for the eighth kept
+        // small jobs on a few wavefronts (a sort of 100,003 keys 3.0 -> 1.8 ms,
+        // a batch of 27,518 tasks 0.64 -> 0.45 ms).  Later it would cost large
         // jobs 2 to 3 % at their ends, and the FMM list traversal, whose pairs
         // fan out eightfold, fills the grid without it and pays for the frames
-        // (2.3 -> 2.7 ms).
+        // (2.3 -> 2.7 ms).  The eighths count from the start: without them
+        // grids that are never three quarters idle (few wavefronts, or more
+        // than are resident at once) exposed nothing for 16 looks (two
+        // wavefronts per group, 10 queens: 0.37 ms without early looks, 0.56
+        // without the eighths, 0.38; 64 wavefronts, fib(20): 0.36, 0.37, 0.29).
         int32_t c = 0;
         if (ln == 0) c = ld_relaxed(&deque_meta(p, me, 0)->count);
         if (ln == 1) c = ld_relaxed(&p.ctl->hungry);
         const int32_t own = __builtin_amdgcn_readlane(c, 0), seekers = __builtin_amdgcn_readlane(c, 1);
-        uint32_t give = own < static_cast<int32_t>(kWave) && seekers > 0 ? have / 2 : 0u;
-        if (kRamp && xmask == 0) {
-          if (give > kWave) give = kWave;
-          if (seekers * 4 < static_cast<int32_t>(p.nwaves) * 3) give = 0;
-          if (--ramp_left == 0) xmask = kExposeMask;
+        uint32_t give = 0;
+        if (own < static_cast<int32_t>(kWave) && seekers > 0) {
+          if (regular) give = have / 2;
+          else if (seekers * 4 >= static_cast<int32_t>(p.nwaves) * 3) give = have / 2 < kWave ? have / 2 : kWave;
         }
+        if (early) --ramp_left;
         if (give > ex) ex = give;
       }
       E = ex;
