@@ -786,6 +786,28 @@ GTAP_DEV void run_search(const Params &p, Lds &S, uint64_t todo, uint32_t tid, O
       J = load_job(p.jobs + kj);
       cur_job = kj;
       cur_u = cur_par = kNone;
+      if (J.pivot || J.kk > 5) {
+        // the job's edges with too few candidates, by their own lanes (run_sets
+        // looks at its rows itself): where thresholds are small half of all
+        // these tasks end so (30,000 vertices, threshold 16, pivoting: k = 6 8.4
+        // -> 7.7 ms; run one after another they made such calls slower than a
+        // lane for each task, 4.9 and 7.3 ms at k = 4 and 6)
+        bool done = false;
+        if (((1ull << k | todo) >> ln & 1u) != 0 && o.job == kj && o.kind == TK_KS_EDGE) {
+          const uint32_t u = o.d[0], W = (static_cast<uint32_t>(J.rp[u + 1] - J.rp[u]) + 63) / 64;
+          const uint64_t *row = J.mat + (J.n + 1) + co_ld64(J.mat + u) + static_cast<size_t>(o.d[1]) * W;
+          uint32_t c = 0;
+          for (uint32_t w = 0; w < W; ++w) c += __popcll(co_ld64(row + w));
+          done = c < J.kk;
+          if (done) {
+            o.value = 0;
+            o.words = 4 + 2 * W;  // row bounds, matrix offset, the edge's row
+          }
+        }
+        const uint64_t m = ballot(done);
+        todo &= ~m;
+        if ((m >> k) & 1u) continue;
+      }
     }
     if (ku != cur_u) {
       M = load_mat(J, ku);
@@ -870,6 +892,7 @@ GTAP_DEV void run_search(const Params &p, Lds &S, uint64_t todo, uint32_t tid, O
     // what to do with the candidate set: finished (val), counted in place or split
     int64_t val = 0;
     enum { kDone, kPairs, kCount, kSplit, kHeavy } act = kDone;
+    uint32_t few = 0;  // pivoting, in place: members still to be chosen, when at most two
     if (kind == TK_KS_HEAVY) {
       act = kSplit;
       words += J.pivot ? 2 * W * (c + 1) + 2 + 4 * W : 2 + 2 * W;  // pivot rows; node state
@@ -878,6 +901,11 @@ GTAP_DEV void run_search(const Params &p, Lds &S, uint64_t todo, uint32_t tid, O
       else if (node && c == 0) val = kcs::binom(q, J.kk - h);
       else if (c + q >= J.kk - h) act = c <= J.thr ? kCount : node ? kSplit : kHeavy;
       if (act == kCount || act == kSplit) words += 2 * W * (c + (node && ki != 0 ? 1 : 0));  // the candidates' rows (and R)
+      if (act == kCount && J.kk - h <= 2) {  // from the candidates and the q pivots, which all are neighbours (k = 4: 5.6 -> 1.6 ms)
+        few = J.kk - h;
+        act = few == 2 ? kPairs : kDone;
+        if (few == 1) val = c + q;
+      }
     } else {
       if (l == 1) val = c;
       else if (c >= l) act = l == 2 ? kPairs : c <= J.thr ? kCount : node ? kSplit : kHeavy;
@@ -891,6 +919,7 @@ GTAP_DEV void run_search(const Params &p, Lds &S, uint64_t todo, uint32_t tid, O
           for (uint32_t v = 0; v < W; ++v) e += __popcll(word(w * 64 + ln, v) & word_of(s, v));
       }
       val = wave_sum(e);
+      if (few == 2) val = val / 2 + static_cast<int64_t>(c) * q + static_cast<int64_t>(q) * (q - 1) / 2;  // rows hold both directions
     } else if (act == kCount) {
       // the candidates, one per lane
       wave_sync();
