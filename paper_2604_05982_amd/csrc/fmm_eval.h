@@ -16,18 +16,21 @@ namespace fmm {
 
 constexpr uint32_t kM2LThreads = 64;
 
-// Workgroup -> position in a list sorted by target.  Workgroups go round-robin
-// to the eight XCDs, each with an L2 of its own; runs of `run` consecutive
-// positions stay on one XCD, so that neighbouring targets find the sources
-// they share there.  The grid is a multiple of 8 * run (positions past the
-// end have no work).
+// Workgroup -> M2L target.  Workgroups go round-robin to the eight XCDs, each
+// with an L2 of its own; runs of kM2LRun consecutive targets stay on one XCD, so
+// that neighbours find the sources they share there.  The grid is a multiple of
+// 8 * kM2LRun (positions past the end have no work).  Runs must be short next to
+// the tree, or small jobs leave XCDs idle: k_m2l_list with runs of 1, 16, 64 and
+// 256 takes 23, 23, 23 and 31 us for 504 cells (10,000 points), 156, 157, 160
+// and 159 us for 6,260, and 3.86, 3.82, 3.78 and 3.77 ms for 145,571 (4 M
+// points).  P2P gains nothing from runs (16.8 ms for 4 M points with and
+// without; runs of 64 workgroups: 0.11 -> 0.16 ms for 10,000).
 constexpr uint32_t kXcds = 8;
-GTAP_DEV uint32_t xcd_position(uint32_t block, uint32_t run) {
+constexpr uint32_t kM2LRun = 16;
+GTAP_DEV uint32_t m2l_target(uint32_t block) {
   const uint32_t xcd = block % kXcds, i = block / kXcds;
-  return (i / run * kXcds + xcd) * run + i % run;
+  return (i / kM2LRun * kXcds + xcd) * kM2LRun + i % kM2LRun;
 }
-constexpr uint32_t kM2LRun = 256;  // targets
-constexpr uint32_t kP2PRun = 64;   // workgroups of 256 list entries
 
 // The 49 derivatives T'_g = d^g (1/|d|) with g_z <= 1 (|g| <= 6), times `unit`:
 // the Coulomb three-term recurrence multiplied by g! becomes
@@ -141,7 +144,7 @@ __global__ __launch_bounds__(kM2LThreads, 2) void k_m2l_list(const int32_t *__re
   constexpr uint32_t kUnits = kHalf / 2;          // 16-byte units of it
   static_assert(kHalf % 2 == 0 && kHalf >= nred(4) && kHalf >= kNr - nred(4), "halves of a row");
   __shared__ double2 rows[kWave * kUnits];
-  const uint32_t a = xcd_position(blockIdx.x, kM2LRun);
+  const uint32_t a = m2l_target(blockIdx.x);
   if (a >= ncells) return;
   const uint64_t lo = seg_lo[a], hi = seg_hi[a];
   const uint32_t ln = threadIdx.x;
@@ -231,7 +234,7 @@ __global__ __launch_bounds__(kP2PThreads) void k_p2p_list(const int32_t *__restr
   __shared__ uint32_t mark[W][kWave];
   const uint32_t tx = threadIdx.x, ln = tx % kWave;
   const uint32_t wv = __builtin_amdgcn_readfirstlane(tx / kWave);
-  const uint64_t e0 = (static_cast<uint64_t>(xcd_position(blockIdx.x, kP2PRun)) * W + wv) * kWave;
+  const uint64_t e0 = (static_cast<uint64_t>(blockIdx.x) * W + wv) * kWave;
   if (e0 >= n) return;
   const uint32_t ne = static_cast<uint32_t>(min(static_cast<uint64_t>(kWave), n - e0));
   double2 *const st = stage[wv];

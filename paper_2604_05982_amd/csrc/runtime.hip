@@ -869,8 +869,8 @@ bool dev_alloc(gtap_ctx *c, T **p, size_t count) {
 
 unsigned nblk(int64_t n, unsigned b) { return static_cast<unsigned>(std::max<int64_t>((n + b - 1) / b, 1)); }
 
-// Workgroups of a grid of n positions in runs of `run` per XCD (fmm::xcd_position).
-unsigned xcd_grid(int64_t n, unsigned run) { return nblk(n, fmm::kXcds * run) * fmm::kXcds * run; }
+// Workgroups of k_m2l_list (fmm::m2l_target).
+unsigned m2l_grid(int64_t ncells) { return nblk(ncells, fmm::kXcds * fmm::kM2LRun) * fmm::kXcds * fmm::kM2LRun; }
 
 // Interaction-list capacities: the caller's, else an estimate from the number
 // of cells and theta (100 M2L and 30 P2P pairs per cell at theta = 1, growing
@@ -1150,12 +1150,12 @@ int fmm_eval_lists(gtap_ctx *c, FmmJobMem &m, uint64_t n_m2l, uint64_t n_p2p, gt
   if (hipEventRecord(m.lev[2], st) != hipSuccess) return GTAP_E_HIP;
   if ((rc = prepare(m.m2l, n_m2l, &D->m2l_hash, &D->m2l_pairs))) return rc;
   if (hipEventRecord(m.lev[3], st) != hipSuccess) return GTAP_E_HIP;
-  hipLaunchKernelGGL(fmm::k_m2l_list, dim3(xcd_grid(m.ncells, fmm::kM2LRun)), dim3(fmm::kM2LThreads), 0, st, m.hdesc.cell, m.hdesc.Qr,
+  hipLaunchKernelGGL(fmm::k_m2l_list, dim3(m2l_grid(m.ncells)), dim3(fmm::kM2LThreads), 0, st, m.hdesc.cell, m.hdesc.Qr,
                      m.hdesc.Lr, m.sorted, lo, hi, static_cast<uint32_t>(m.ncells));
   if (hipEventRecord(m.lev[4], st) != hipSuccess) return GTAP_E_HIP;
   if ((rc = prepare(m.p2p, n_p2p, &D->p2p_hash, &D->p2p_pairs))) return rc;
   if (hipEventRecord(m.lev[5], st) != hipSuccess) return GTAP_E_HIP;
-  hipLaunchKernelGGL(fmm::k_p2p_list, dim3(xcd_grid(nblk(static_cast<int64_t>((n_p2p + kWave - 1) / kWave), fmm::kP2PThreads / kWave), fmm::kP2PRun)),
+  hipLaunchKernelGGL(fmm::k_p2p_list, dim3(nblk(static_cast<int64_t>((n_p2p + kWave - 1) / kWave), fmm::kP2PThreads / kWave)),
                      dim3(fmm::kP2PThreads), 0, st, m.hdesc.cell, m.hdesc.px, m.hdesc.py, m.hdesc.pz, m.hdesc.pq,
                      m.hdesc.phi, m.sorted, n_p2p, static_cast<uint32_t>(m.ncells), &D->p2p_inter, &D->coincident);
   if (hipEventRecord(m.lev[6], st) != hipSuccess) return GTAP_E_HIP;
