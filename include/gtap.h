@@ -321,12 +321,18 @@ int gtap_submit(gtap_ctx *ctx, int32_t kind, const void *args, size_t args_bytes
 /* Launch one persistent kernel for every pending job on cfg->stream and wait
  * for it.  Jobs' results become readable with gtap_result.  FMM jobs also run
  * their tree construction and upward pass before, and their downward pass
- * after, that launch (device memory for them is allocated inside this call
- * and kept by the context for its next runs, up to 8 GB).  Returns GTAP_E_CAPACITY or GTAP_E_TIMEOUT when the device
- * aborted the run (results of that run are then invalid; the context stays
- * usable), GTAP_E_INVAL when an FMM job's points leave the root cube,
- * GTAP_E_NOMEM, GTAP_E_HIP on a HIP failure. */
+ * after, that launch.  Device memory for them and for split k-clique jobs is
+ * allocated inside this call and kept by the context for its next runs, up to
+ * 8 GB (gtap_release gives it back).  Returns GTAP_E_CAPACITY or
+ * GTAP_E_TIMEOUT when the device aborted the run (results of that run are then
+ * invalid; the context stays usable), GTAP_E_INVAL when an FMM job's points
+ * leave the root cube, GTAP_E_NOMEM, GTAP_E_HIP on a HIP failure. */
 int gtap_run(gtap_ctx *ctx);
+
+/* Give the device memory that the context keeps between runs back to the
+ * device, for other contexts and allocators; the next run that needs such
+ * memory allocates it again.  Errors: GTAP_E_INVAL, GTAP_E_STATE (serving). */
+int gtap_release(gtap_ctx *ctx);
 
 /* Copy job job_id's result into host memory out: an int64 count
  * (out_bytes >= 8), or for an FMM job a gtap_fmm_result (out_bytes >= its

@@ -247,7 +247,7 @@ int fill_params(const gtap_config &cfg, uint32_t nw, const Layout &L, char *ws, 
 // long as everything else around the kernels of a 10^5-point FMM job.  A run
 // takes the smallest unused buffer that fits and is at most twice as large;
 // what is unused at its end beyond kCacheBytes goes back to the device, the
-// rest with the context.  Reuse is safe because a context belongs to one host
+// rest with gtap_release or the context.  Reuse is safe because a context belongs to one host
 // thread and a run ends only when its stream is idle.
 constexpr size_t kCacheBytes = 8ull << 30;
 
@@ -1713,6 +1713,13 @@ int gtap_result(gtap_ctx *c, uint64_t job_id, void *out, size_t out_bytes) {
     return GTAP_E_PENDING;
   if (job_id < c->next_job_id) return GTAP_E_PENDING;
   return GTAP_E_NOJOB;
+}
+
+int gtap_release(gtap_ctx *c) {
+  if (!c) return GTAP_E_INVAL;
+  if (c->serving) return GTAP_E_STATE;  // freeing waits for the device
+  c->cache.trim(0);
+  return GTAP_OK;
 }
 
 int gtap_finalize(gtap_ctx *c) {

@@ -217,6 +217,7 @@ def _load() -> ctypes.CDLL:
     lib.gtap_kclique_split_buffer_ints.restype = ctypes.c_int32
     lib.gtap_result.argtypes = [vp, ctypes.c_uint64, vp, ctypes.c_size_t]
     lib.gtap_finalize.argtypes = [vp]
+    lib.gtap_release.argtypes = [vp]
     lib.gtap_stats_get.argtypes = [vp, P(gtap_stats)]
     lib.gtap_last_error.argtypes = [vp, P(gtap_error_report)]
     lib.gtap_status_string.argtypes = [ctypes.c_int32]
@@ -236,7 +237,7 @@ def _load() -> ctypes.CDLL:
     lib.gtap_run_static.argtypes = [P(gtap_config), P(gtap_trace_job), ctypes.c_size_t, P(ctypes.c_int64),
                                     P(gtap_error_report)]
     for fn in ("gtap_workspace_size", "gtap_init", "gtap_submit", "gtap_run", "gtap_result",
-               "gtap_finalize", "gtap_stats_get", "gtap_last_error", "gtap_serve_start",
+               "gtap_finalize", "gtap_release", "gtap_stats_get", "gtap_last_error", "gtap_serve_start",
                "gtap_serve_submit", "gtap_serve_poll", "gtap_serve_stop", "gtap_trace_run",
                "gtap_trace_run_plain", "gtap_autotune", "gtap_probe_atomics",
                "gtap_litmus", "gtap_run_static"):
@@ -251,7 +252,8 @@ EXPORTED = ("gtap_config_default", "gtap_workspace_size", "gtap_init", "gtap_sub
             "gtap_result", "gtap_finalize", "gtap_stats_get", "gtap_last_error",
             "gtap_status_string", "gtap_serve_start", "gtap_serve_submit", "gtap_serve_poll",
             "gtap_serve_stop", "gtap_trace_run", "gtap_trace_run_plain", "gtap_autotune",
-            "gtap_kclique_split_buffer_ints", "gtap_probe_atomics", "gtap_litmus", "gtap_run_static")
+            "gtap_kclique_split_buffer_ints", "gtap_probe_atomics", "gtap_litmus", "gtap_run_static",
+            "gtap_release")
 
 
 class GtapError(RuntimeError):
@@ -329,6 +331,12 @@ def gtap_stats_get(ctx) -> dict:
     if rc != GTAP_OK:
         raise GtapError(rc, "gtap_stats_get")
     return st.as_dict()
+
+
+def gtap_release(ctx) -> None:
+    rc = _lib.gtap_release(ctx)
+    if rc != GTAP_OK:
+        raise GtapError(rc, "gtap_release")
 
 
 def gtap_finalize(ctx) -> None:
@@ -655,6 +663,10 @@ class Runtime:
 
     def last_error(self) -> dict:
         return gtap_last_error(self.ctx)
+
+    def release(self) -> None:
+        """Give the device memory kept for later runs back to the device."""
+        gtap_release(self.ctx)
 
     def close(self) -> None:
         if getattr(self, "ctx", None) is not None:
