@@ -948,8 +948,11 @@ int fmm_prepare(gtap_ctx *c, const gtap_fmm_args &a, FmmJobMem &m) {
       if (hipMemcpyAsync(c2, m.cell, sizeof(int32_t) * fmm::kCellInts * hi, hipMemcpyDeviceToDevice, st) !=
               hipSuccess ||
           hipMemcpyAsync(p2, m.parent, sizeof(int32_t) * hi, hipMemcpyDeviceToDevice, st) != hipSuccess ||
-          hipStreamSynchronize(st) != hipSuccess)
+          hipStreamSynchronize(st) != hipSuccess) {
+        c->cache.put(c2);
+        c->cache.put(p2);
         return GTAP_E_HIP;
+      }
       c->cache.put(m.cell);
       c->cache.put(m.parent);
       m.cell = c2;
