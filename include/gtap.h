@@ -103,17 +103,18 @@ typedef struct {
  * out-neighbour v: the edge's candidates N+(u) /\ N+(v) are row v, and it
  * counts the (k-2)-cliques among them (k = 3: the size of the intersection).
  * A vertex with at most `threshold` out-neighbours counts all its edges in
- * place instead.  gtap_run allocates the job's matrices for the run: sum over
+ * place instead.  gtap_run provides the job's matrices for the run: sum over
  * the vertices that fork of d * ceil(d/64) * 8 bytes (twice that for
  * pivoting), d = out-degree.
  * A search node whose candidate set has more than
  * `threshold` members splits into one child task per branch -- per candidate
  * for the orientation algorithm; the pivot and each of its non-neighbours for
  * pivoting -- and every child applies the same test; smaller nodes are
- * counted in place by one lane.  Same graph contract as gtap_kclique_args
- * (row_ptr_dev/col_dev borrowed until gtap_run returns, sorted acyclic
- * out-lists); the library reads row_ptr once at submit and rejects a graph
- * whose largest out-degree exceeds max_outdeg or 1024.  Needs thread mode,
+ * counted in place.  Same graph contract as gtap_kclique_args (row_ptr_dev /
+ * col_dev borrowed until gtap_run returns, sorted out-lists of any acyclic
+ * orientation); the library reads row_ptr at submit, where it rejects a graph
+ * whose largest out-degree exceeds max_outdeg or 1024 and sizes the matrices,
+ * and again in gtap_run: it must not change in between.  Needs thread mode,
  * waves_per_group 4, flags 0, 1 <= k <= 32, 0 <= threshold <= 64 and, for
  * k >= 4, big frames of at least gtap_kclique_split_buffer_ints(max_outdeg)
  * ints.  The result is the number of k-cliques. */
@@ -211,8 +212,8 @@ typedef struct {
 
 /* Cilksort (Sec. 6.3, microbenchmarks): sorts keys_dev[0, n) in place with a
  * parallel mergesort whose merges are split in parallel too.  sort(lo, n)
- * sorts ranges of at most sort_cutoff keys serially (a 64-wide sorting network
- * on one lane), otherwise sorts both halves into the other buffer and merges
+ * sorts ranges of at most sort_cutoff keys in one task (a sorting network over
+ * a wavefront's lanes), otherwise sorts both halves into the other buffer and merges
  * them back; a merge of more than merge_cutoff keys splits the longer range at
  * its middle key and the other by binary search into two independent merges.
  * tmp_dev is a scratch buffer of n keys.  Both are device arrays borrowed

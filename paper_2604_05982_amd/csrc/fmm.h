@@ -52,7 +52,6 @@ struct Tables {
   uint8_t idx[kP + 1][kP + 1][kP + 1];   // inverse of e
   uint8_t deg[kNc];
   uint8_t dm1[kNc][3];                   // index of g - e_i (0xFF if g_i == 0)
-  uint8_t dm2[kNc][3];                   // index of g - 2 e_i (0xFF if g_i < 2)
   uint8_t red[kNr];                      // coefficient of reduced index r
   uint8_t red_of[kNc];                   // inverse (0xFF: z exponent >= 2)
   uint8_t g_of[kP + 1][kP + 1][3];       // index of derivative (x, y, z <= 2) among the 64
@@ -86,14 +85,9 @@ constexpr Tables make_tables() {
     for (int i = 0; i < 3; ++i) {
       int g[3] = {T.e[s][0], T.e[s][1], T.e[s][2]};
       T.dm1[s][i] = 0xFF;
-      T.dm2[s][i] = 0xFF;
       if (g[i] >= 1) {
         g[i] -= 1;
         T.dm1[s][i] = T.idx[g[0]][g[1]][g[2]];
-        if (g[i] >= 1) {
-          g[i] -= 1;
-          T.dm2[s][i] = T.idx[g[0]][g[1]][g[2]];
-        }
       }
     }
   int r = 0;

@@ -14,9 +14,9 @@
 // A node of the search splits when its candidate set is larger than the
 // threshold t (the spawn-time cost estimate): it stores its state in its frame
 // and forks one task per branch, and every child applies the same test.  A
-// node at or below the threshold is finished in place: its candidates are
-// renumbered into a 64 x 64 matrix (one word per row) in LDS and the lanes of
-// the wavefront share the search (kclique_wave.h).
+// node at or below the threshold is finished in place: the lanes of the
+// wavefront share the search, in the vertex's matrix or with the candidates
+// renumbered into a 64 x 64 matrix (one word per row) in LDS (kclique_wave.h).
 //
 //   orientation   node (S, l) counts l-cliques of the DAG on S:
 //                 K(S,1) = |S|, K(S,l) = sum over x in S of K(S /\ row x, l-1)
@@ -29,8 +29,8 @@
 //                 remain after removing p and the earlier non-neighbours.
 //
 // The bit matrices of all vertices of a job live in one device buffer the
-// library allocates per run, after n+1 per-vertex offsets (64-bit words)
-// computed on the host from row_ptr: vertex u's D, then for pivoting its U.
+// library takes per run, after n+1 per-vertex offsets (64-bit words) computed
+// on the device from row_ptr: vertex u's D, then for pivoting its U.
 // A node task's big-frame buffer holds only its node state: one 64-bit meta
 // word (level or held count | pivots << 16 | pivot << 32), the candidate set
 // P (W words), pivoting's branch set R (W words: the pivot's non-neighbours

@@ -684,7 +684,7 @@ GTAP_DEV void make_child(uint32_t ckind, const Words<6> &d, uint32_t j, ChildIni
         c.p[1] = d[1];
         return;
       }
-      if (ckind == TK_KS_NODE) {  // (vertex, branch, parent's node-state offset)
+      if (ckind == TK_KS_NODE) {  // (vertex, branch); d[1] is 0
         c.p[0] = d[0];
         c.p[1] = j;
         c.p[2] = d[1];
