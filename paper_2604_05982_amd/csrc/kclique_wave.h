@@ -54,35 +54,80 @@ namespace gtap {
 // the shorter list: a vertex with 4,000 out-neighbours of out-degree 1, k = 3,
 // 5.57 -> 0.38 ms; 20,000 vertices of mean degree 30 in random order, k = 5,
 // 2.74 -> 1.62 ms.  Turning only at half or a quarter of C's length measured the
-// same or up to 8 % slower.  Where almost every element is found next to the one
-// before, a walk by each lane is still the faster one (3,000 vertices joined to
-// the next 128, k = 3: 1.1 ms walked, 1.7 ms this way).
+// same or up to 8 % slower.
+//
+// From two rounds of the stream on, both lists are first cut to the elements
+// between the other's ends (four bisections side by side, about one round's
+// time): lists of neighbouring ids overlap in a part only, and there a walk that
+// finds each element next to the one before needs few loads.  3,000 vertices
+// joined to the next 128, k = 3: 1.09 ms walked, 1.67 without the cut, 1.14; k = 7
+// on 300,000 vertices 59.1 -> 54.1 ms.  From four or eight rounds on: 55.4, 56.8.
 GTAP_DEV void run_cands(const Params &p, uint32_t *mark, uint64_t todo, uint32_t tid, Outcome &o) {
   constexpr uint32_t kFlight = 4;  // 64-element chunks in flight
+  constexpr uint32_t kCut = 2 * kFlight * kWave;  // elements streamed from which the lists are cut first
   const uint32_t ln = lane_id();
   const bool mine = ((todo >> ln) & 1u) != 0;
   const bool turn = mine && o.d[5] < o.d[4];
   // streamed: n elements at (d0, d1); searched: nb elements at (d2, d3)
-  const uint32_t n = mine && o.d[4] > 0 && o.d[5] > 0 ? (turn ? o.d[5] : o.d[4]) : 0u;
-  const uint32_t nb = mine ? (turn ? o.d[4] : o.d[5]) : 0u;
-  const uint32_t d0 = turn ? o.d[2] : o.d[0], d1 = turn ? o.d[3] : o.d[1];
-  const uint32_t d2 = turn ? o.d[0] : o.d[2], d3 = turn ? o.d[1] : o.d[3];
+  uint32_t n = mine && o.d[4] > 0 && o.d[5] > 0 ? (turn ? o.d[5] : o.d[4]) : 0u;
+  uint32_t nb = mine ? (turn ? o.d[4] : o.d[5]) : 0u;
+  uint32_t d0 = turn ? o.d[2] : o.d[0], d1 = turn ? o.d[3] : o.d[1];
+  uint32_t d2 = turn ? o.d[0] : o.d[2], d3 = turn ? o.d[1] : o.d[3];
   const uint64_t turned = ballot(turn);
   const uint32_t left = o.nchild;  // levels left; 1: count only
   uint64_t dst = 0;
   if (n > 0 && left > 1) dst = reinterpret_cast<uint64_t>(frame_ptr(p, tid) + FW_BUF);
   uint32_t total = 0;
-  const uint32_t off = wave_exclusive_scan(n, &total);
-  uint32_t longest = nb;
-  for (uint32_t i = 1; i < kWave; i <<= 1) {
-    const uint32_t y = static_cast<uint32_t>(__shfl_xor(static_cast<int>(longest), static_cast<int>(i), 64));
-    longest = y > longest ? y : longest;
-  }
-  longest = uniform(longest);
+  uint32_t off = wave_exclusive_scan(n, &total);
+  auto wave_max = [](uint32_t x) {
+    for (uint32_t i = 1; i < kWave; i <<= 1) {
+      const uint32_t y = static_cast<uint32_t>(__shfl_xor(static_cast<int>(x), static_cast<int>(i), 64));
+      x = y > x ? y : x;
+    }
+    return uniform(x);
+  };
+  uint32_t longest = wave_max(nb);
   auto from = [](uint32_t x, uint32_t k) {
     return static_cast<uint32_t>(__shfl(static_cast<int>(x), static_cast<int>(k), 64));
   };
   auto read = [](bool coherent, const int32_t *a) { return coherent ? co_ld32i(a) : *a; };
+  if (total >= kCut) {
+    // at[0, 1]: the streamed list's elements from the other's first one on and
+    // up to its last one; at[2, 3]: the other way round
+    const int32_t *S = reinterpret_cast<const int32_t *>(pack(d0, d1));
+    const int32_t *B = reinterpret_cast<const int32_t *>(pack(d2, d3));
+    uint32_t at[4] = {0, 0, 0, 0};
+    int32_t v[4] = {0, 0, 0, 0};
+    if (n > 0) {
+      v[0] = read(turn, B);
+      v[1] = read(turn, B + nb - 1) + 1;
+      v[2] = read(!turn, S);
+      v[3] = read(!turn, S + n - 1) + 1;
+    }
+    const uint32_t top = wave_max(n > 0 ? (n > nb ? n : nb) : 1u);
+    for (uint32_t step = 1u << (31 - __builtin_clz(top)); step > 0; step >>= 1) {
+      int32_t y[4];
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) {
+        const uint32_t len = n > 0 ? (q < 2 ? n : nb) : 0u;
+        y[q] = at[q] + step <= len ? read(q < 2 ? !turn : turn, (q < 2 ? S : B) + (at[q] + step - 1)) : 0x7FFFFFFF;
+      }
+#pragma unroll
+      for (uint32_t q = 0; q < 4; ++q) {
+        const uint32_t len = n > 0 ? (q < 2 ? n : nb) : 0u;
+        at[q] += at[q] + step <= len && y[q] < v[q] ? step : 0u;
+      }
+    }
+    S += at[0];
+    B += at[2];
+    n = at[1] > at[0] && at[3] > at[2] ? at[1] - at[0] : 0u;
+    nb = n > 0 ? at[3] - at[2] : 0u;
+    const uint64_t s64 = reinterpret_cast<uint64_t>(S), b64 = reinterpret_cast<uint64_t>(B);
+    d0 = static_cast<uint32_t>(s64); d1 = static_cast<uint32_t>(s64 >> 32);
+    d2 = static_cast<uint32_t>(b64); d3 = static_cast<uint32_t>(b64 >> 32);
+    off = wave_exclusive_scan(n, &total);
+    longest = wave_max(nb);
+  }
   uint32_t carry = 0, found = 0;
   for (uint32_t c0 = 0; c0 < total; c0 += kFlight * kWave) {
     uint32_t own[kFlight], at[kFlight], len[kFlight];

@@ -57,3 +57,31 @@ def test_hub_of_short_lists_is_not_quadratic():
             return min(times)
 
         assert ms(4000) < 8 * ms(250)
+
+
+@pytest.mark.parametrize("labels", ["ascending", "descending", "random"])
+def test_lists_cut_to_their_overlap(labels):
+    """Lists of neighbouring ids, which overlap in all, a part or nothing, in
+    streams on both sides of the 512 elements from which they are cut, and ids
+    that do not ascend along the edges."""
+    from paper_2604_05982_amd import gtap
+    rng = np.random.default_rng(17)
+    with gtap.Runtime(timeout_ms=60000, num_waves=64, small_frames=1 << 20, big_frames=1 << 18, big_frame_ints=320) as rt:
+        for n, w in ((20, 7), (60, 8), (70, 9), (200, 8), (300, 30), (150, 64), (170, 70), (140, 130)):
+            e = np.array([(i, i + j) for i in range(n) for j in range(1, w + 1) if i + j < n])
+            g = graphs.oriented_from_edges(n, e, order="id")
+            ids = {"ascending": np.arange(n), "descending": np.arange(n)[::-1], "random": rng.permutation(n)}[labels]
+            src = np.repeat(np.arange(n), np.diff(g.row_ptr))
+            u, v = ids[src], ids[g.col[: src.size]]
+            at = np.lexsort((v, u))
+            rp = np.concatenate([[0], np.cumsum(np.bincount(u, minlength=n))]).astype(np.int32)
+            col = v[at].astype(np.int32)
+            for k in (3, 4, 5) if w < 60 else (3, 4):
+                want = oracle.kclique(rp, col, k)
+                assert want.value == oracle.kclique(g.row_ptr, g.col, k).value
+                print(f"{labels} {n} vertices, {w} next, k {k}", flush=True)
+                job = rt.submit_kclique(rp, col, k, range_leaf=64)
+                rt.run()
+                st = rt.stats()
+                assert rt.result(job) == want.value
+                assert (st["tasks"], st["conts"]) == (want.tasks, want.conts)
